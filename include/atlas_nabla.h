@@ -325,7 +325,9 @@ typedef struct {
   int32_t nodes_per_wave;   /* node groups a wave handles per workgroup       */
   int32_t blocks_per_cu;    /* persistent grid = blocks_per_cu * CU count     */
   int32_t xcd_remap;        /* 1: each XCD walks a contiguous part of the
-                               node order (the default), 2: plain order      */
+                               node order (the default, but for one-tile
+                               LDS workgroups), 2: plain order (their
+                               default)                                      */
   int32_t lanes_per_node;   /* 16, 32 or 64 lanes share a column (nlev > 32);
                                columns of <= 32 levels always use nlev lanes */
   int32_t slices_per_iter;  /* level slices in flight per lane, 1..3         */
@@ -335,7 +337,8 @@ typedef struct {
                                32); LDS tiles: rows per tile (default 4)      */
   int32_t run_nodes;        /* consecutive nodes of a row per run (default 16,
                                64 on the row-window walk); LDS tiles: bands
-                               swept together by longitude (default 8)        */
+                               swept together by longitude (default 8; the
+                               library's own tile shapes mostly take 1)       */
   int32_t nt_stores;        /* 1: non-temporal output stores, 2: plain (the
                                default)                                      */
   int32_t row_window;       /* 1-ring operators on columns of more than 32

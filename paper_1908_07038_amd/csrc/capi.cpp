@@ -241,7 +241,7 @@ void shape_out(const Shape& s, atlas_tune_t* t) {
   t->waves_per_block = s.waves_per_block;
   t->nodes_per_wave = s.nodes_per_wave;
   t->blocks_per_cu = s.blocks_per_cu;
-  t->xcd_remap = s.xcd_remap ? 1 : 2;
+  t->xcd_remap = s.xcd_remap < 0 ? 0 : s.xcd_remap ? 1 : 2;
   t->lanes_per_node = s.lanes_per_node;
   t->slices_per_iter = s.slices_per_iter;
   t->band_rows = s.band_rows;
@@ -329,7 +329,8 @@ int run_op(atlas_mesh_t mesh, int op, int dtype, int32_t nlev, const void* in, v
   if (overlaps(in, nin, out, nout)) return fail(ATLAS_EINVAL, "output overlaps input");
   DeviceGuard g(mesh->device);
   if (!g.ok) return fail(ATLAS_EHIP, "cannot select the mesh's device");
-  Shape sh = resolve_shape(op, dtype, nlev, shape_override ? *shape_override : mesh->shape[op][dtype]);
+  const Shape& asked = shape_override ? *shape_override : mesh->shape[op][dtype];
+  Shape sh = resolve_shape(op, dtype, nlev, asked);
   TileGeom tg = uses_tiles(op, dtype, nlev, sh) ? tile_geom(op, dtype, nlev, sh) : TileGeom();
   // BF16 tiles copy whole dwords around each column segment: they need a
   // 4-byte aligned field (else the row-window walk or gather runs)
@@ -352,7 +353,10 @@ int run_op(atlas_mesh_t mesh, int op, int dtype, int32_t nlev, const void* in, v
     if (e != hipSuccess) return hip_fail(e, kOpName[op]);
     return ATLAS_OK;
   }
-  // the row-window walk works best on long runs
+  // no tiles: their order's defaults do not apply; the row-window walk works
+  // best on long runs
+  sh.run_nodes = asked.run_nodes;
+  if (asked.xcd_remap < 0) sh.xcd_remap = 1;
   if (sh.run_nodes == 0 && uses_window(op, nlev, sh)) sh.run_nodes = kDefaultWindowRunNodes;
   NodeOrder order;
   try {
@@ -1135,7 +1139,8 @@ int plan_op(atlas_batch_s* b, int o, BatchOp& bo, bool pair = false) {
   int Lmax = 1;
   for (const atlas_tracer_desc_t& d : b->descs) Lmax = std::max(Lmax, d.nlev);
   // tile defaults of the long-column launch, also for batches of short columns
-  const Shape sh = resolve_shape(k, b->dtype, std::max(Lmax, 33), b->shape[o]);
+  Shape sh = resolve_shape(k, b->dtype, std::max(Lmax, 33), b->shape[o]);
+  sh.run_nodes = b->shape[o].run_nodes;   // each XCD walks a share of its own: the default sweep keeps its halo rows in L2
   if (sh.lds_tiles != 3) return ATLAS_OK;
   const int ntr = (int)b->descs.size();
   std::map<int, std::pair<DevTiles, const void*>> tilings;

@@ -42,7 +42,7 @@ struct Shape {
   int waves_per_block = 4;   // 64-lane waves per workgroup
   int nodes_per_wave = 1;    // node groups per wave per workgroup
   int blocks_per_cu = 4;     // persistent kernels only
-  int xcd_remap = 1;         // contiguous slices of work per XCD
+  int xcd_remap = -1;        // 1: a contiguous part of the work per XCD, 0: plain order; -1: resolve_shape picks
   int lanes_per_node = 0;    // 0: chosen from nlev; else 16, 32 or 64 (nlev > 32)
   int slices_per_iter = 0;   // 0: 3 (capped by the slice count); else 1..3
   int band_rows = 0;         // 0: kDefaultBandRows; rows per band of the node order
