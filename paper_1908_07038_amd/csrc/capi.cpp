@@ -121,7 +121,7 @@ struct atlas_mesh_s {
   DevTiles tiles(const TileGeom& g, const Shape& sh) {
     const int h = sh.band_rows > 0 ? sh.band_rows : kDefaultTileRows;
     const int sweep = sh.run_nodes > 0 ? sh.run_nodes : kDefaultTileSweep;
-    const std::vector<int64_t> key = {g.ring, h, sweep, g.col_bytes, g.row_bytes, g.budget};
+    const std::vector<int64_t> key = {g.ring, h, sweep, g.col_bytes, g.row_bytes, g.budget, g.block};
     std::lock_guard<std::mutex> lk(order_mu);
     auto it = tilings.find(key);
     if (it != tilings.end()) return it->second;
@@ -130,7 +130,16 @@ struct atlas_mesh_s {
     DevTiles dt;
     // eight pairs of padding: kernels fetch pairs eight at a time
     ht.segs.resize(ht.segs.size() + 16, 0);
-    dt.info = upload(ht.info);
+    std::vector<int32_t> nblk;
+    group_blocks(host_nbr, g.block, ht, nblk);
+    // with the tiles' block counts above their column counts, and their
+    // segment counts above their node counts
+    std::vector<int32_t> info = ht.info;
+    for (int64_t t = 0; t < ht.ntiles; ++t) {
+      info[4 * t + 2] |= nblk[t] << 16;
+      info[4 * t + 3] |= (ht.info[4 * t + 4] - ht.info[4 * t]) << 16;
+    }
+    dt.info = upload(info);
     dt.segs = upload(ht.segs);
     dt.order = upload(ht.order);
     dt.loc = upload(ht.loc);
@@ -151,7 +160,7 @@ struct atlas_mesh_s {
                            hipStream_t stream) {
     const int h = sh.band_rows > 0 ? sh.band_rows : kDefaultTileRows;
     const int sweep = sh.run_nodes > 0 ? sh.run_nodes : kDefaultTileSweep;
-    const std::vector<int64_t> key = {g.ring, h, sweep, g.col_bytes, g.row_bytes, g.budget, op, dtype};
+    const std::vector<int64_t> key = {g.ring, h, sweep, g.col_bytes, g.row_bytes, g.budget, g.block, op, dtype};
     std::lock_guard<std::mutex> lk(order_mu);
     auto it = records.find(key);
     if (it != records.end()) return it->second;

@@ -107,6 +107,7 @@ struct DevTiles {
 struct TileGeom {
   int ring = 1, KL = 0, nchunks = 1;   // KL = 0: no geometry fits the budget
   int64_t col_bytes = 0, row_bytes = 0, budget = 0;
+  int block = 1;   // nodes of a block (see group_blocks)
 };
 // The shape a launch runs with: lds_tiles = 0 picks the path (and tile
 // parameters left at 0) from per-operator, per-dtype defaults.
@@ -118,6 +119,8 @@ void kernel_label(int op, int dtype, int nlev, const Shape& resolved, char* buf,
 TileGeom tile_geom(int op, int dtype, int nlev, const Shape& sh);
 // Bytes of one node record of the tile path (LDS bytes per tile node).
 int64_t tile_record_bytes(int op, int dtype);
+// Nodes a wave evaluates together where their stencils have the regular shape.
+int tile_block_nodes(int op, int dtype);
 // LDS bytes kept free behind a one-tile-per-workgroup buffer: lanes past a
 // column's last level read (and drop) values beyond it, up to the next
 // multiple of 64 U levels of a chunk (chunks of KL levels, the last one

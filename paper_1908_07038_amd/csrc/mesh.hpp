@@ -130,6 +130,16 @@ struct HaloTiles {
 void build_halo_tiles(const HostMesh& m, const OpTables& t, int ring, int band_rows, int run_nodes,
                       int64_t col_bytes, int64_t row_bytes, int64_t budget_bytes, HaloTiles& out);
 
+// Blocks of a tiling: block_nodes consecutive nodes of a row in one tile
+// whose stencils have the regular shape (slots: two consecutive nodes of the
+// row above, left, right, two consecutive nodes of the row below; ring 2:
+// three consecutive nodes two rows up, the outer neighbours of the row above,
+// the own row and the row below, three consecutive nodes two rows down), with
+// every row's first column one further from a node to the next.  Puts each
+// tile's blocks first in its stretch of ht.order (ht.runs keeps the old
+// order); nblk[t] is the number of blocks of tile t.
+void group_blocks(const OpTables& t, int block_nodes, HaloTiles& ht, std::vector<int32_t>& nblk);
+
 // Remapping from an O-grid mesh to the points of a target grid by linear
 // interpolation over the source triangles in 3-D on the sphere (see
 // remap_build.cpp): per target point the three nodes of the triangle its ray

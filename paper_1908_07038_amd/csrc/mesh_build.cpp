@@ -767,4 +767,51 @@ void build_halo_tiles(const HostMesh& m, const OpTables& t, int ring, int band_r
   out.run_off.push_back((int32_t)(out.runs.size() / 2));
 }
 
+void group_blocks(const OpTables& t, int block_nodes, HaloTiles& ht, std::vector<int32_t>& nblk) {
+  if (block_nodes < 0) throw std::runtime_error("block_nodes must be >= 0");
+  struct Cols { int32_t up, lo, uu, ll; };   // first columns of a regular node's rows
+  auto regular = [&](int32_t i, Cols& c) -> bool {
+    const int32_t* nb = &t.nbr8[(size_t)kEll * i];
+    if ((nb[kEll - 1] & 0xff) != 6 || nb[1] != nb[0] + 1 || nb[2] != i - 1 || nb[3] != i + 1 || nb[5] != nb[4] + 1)
+      return false;
+    c = {nb[0], nb[4], 0, 0};
+    if (ht.ring == 1) return true;
+    const int32_t* q = &t.lap_nbr[(size_t)t.lap_stride * i];
+    if (q[t.lap_stride - 1] != 18) return false;
+    c.uu = q[6];
+    c.ll = q[15];
+    const int32_t want[18] = {c.up, c.up + 1, i - 1, i + 1, c.lo, c.lo + 1,
+                              c.uu, c.uu + 1, c.uu + 2, c.up - 1, c.up + 2, i - 2, i + 2,
+                              c.lo - 1, c.lo + 2, c.ll, c.ll + 1, c.ll + 2};
+    return std::equal(want, want + 18, q);
+  };
+  nblk.assign(ht.ntiles, 0);
+  if (block_nodes == 0) return;
+  std::vector<int32_t> rest;
+  for (int64_t tile = 0; tile < ht.ntiles; ++tile) {
+    int32_t* ord = &ht.order[ht.info[4 * tile + 1]];
+    const int n = ht.info[4 * tile + 3];
+    rest.clear();
+    int put = 0;   // block nodes placed so far (at most the nodes read)
+    for (int q = 0; q < n;) {
+      Cols c = {}, e = {};
+      int run = 0;
+      while (run < block_nodes && q + run < n && ord[q + run] == ord[q] + run && regular(ord[q + run], e)) {
+        if (run == 0) c = e;
+        else if (e.up != c.up + run || e.lo != c.lo + run ||
+                 (ht.ring == 2 && (e.uu != c.uu + run || e.ll != c.ll + run))) break;
+        ++run;
+      }
+      if (run == block_nodes) {
+        for (int b = 0; b < run; ++b) ord[put++] = ord[q + b];
+        q += run;
+        ++nblk[tile];
+      } else {
+        rest.push_back(ord[q++]);
+      }
+    }
+    for (int32_t i : rest) ord[put++] = i;
+  }
+}
+
 }  // namespace atlasnabla
