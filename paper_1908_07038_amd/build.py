@@ -50,10 +50,17 @@ def _commands():
            "-Wno-unused-command-line-argument"]
     objs = []
     cmds = []
-    for src, base in (("mesh_build.cpp", host), ("remap_build.cpp", host), ("capi.cpp", host), ("kernels.hip", dev)):
-        obj = os.path.join(BUILD, src + ".o")
+    # kernels.hip: the launches, and once more per element type for that
+    # type's kernels (minutes each, side by side)
+    for src, base, tag, defs in (("mesh_build.cpp", host, "", []), ("remap_build.cpp", host, "", []),
+                                 ("capi.cpp", host, "", []), ("kernels.hip", dev, "", []),
+                                 ("kernels.hip", dev, ".f64", ["-DATLAS_KERNEL_TYPE=double"]),
+                                 ("kernels.hip", dev, ".f32", ["-DATLAS_KERNEL_TYPE=float"]),
+                                 ("kernels.hip", dev, ".bf16", ["-DATLAS_KERNEL_TYPE=bf16_t",
+                                                                "-DATLAS_KERNEL_FIELD_ONLY"])):
+        obj = os.path.join(BUILD, src + tag + ".o")
         objs.append(obj)
-        cmds.append(base + inc + ["-c", os.path.join(CSRC, src), "-o", obj])
+        cmds.append(base + inc + defs + ["-c", os.path.join(CSRC, src), "-o", obj])
     link = [hipcc, "-shared", f"--offload-arch={ARCH}", "-o", LIB + ".tmp"] + objs + \
         ["-Wl,--no-undefined", "-L", os.path.join(ROCM, "lib"), "-lamdhip64"]
     return cmds, link

@@ -122,6 +122,8 @@ __device__ __forceinline__ double2 ld_uniform(const double2* p) {
   return make_double2(ld_const(q), ld_const(q + 1));
 }
 
+}  // namespace
+
 struct Args {
   const int32_t* order; // [V] node processing order (a permutation)
   const int32_t* runs;  // [nruns][2] (first node, count): the same order as row runs
@@ -136,6 +138,8 @@ struct Args {
   int32_t npw;          // node groups (or runs) per wave per workgroup
   int32_t nt;           // non-temporal output stores
 };
+
+namespace {
 
 // ---- one node group per wave --------------------------------------------------
 //
@@ -609,6 +613,8 @@ __global__ __launch_bounds__(256) void k_win(Args a, int64_t nblocks, int remap)
 // Tiles stacked in latitude follow each other, so the halo columns they share
 // are L2 hits.
 
+}  // namespace
+
 struct TileArgs {
   const int32_t* info;   // [ntiles][4]: first segment, first record, columns | blocks << 16, nodes | segments << 16
   const int32_t* segs;   // [nseg (+ 8 padding)][2]: first node, count
@@ -622,6 +628,8 @@ struct TileArgs {
   int32_t nchunks;
   int32_t nt;
 };
+
+namespace {
 
 // Node record of the tile path: coefficient row (8 pairs, ring 1, followed
 // for OP_DIVCURL by the 8 pairs of the second operator, the curl's or, for
@@ -2448,30 +2456,6 @@ hipError_t launch_u(const Args& a, int U, dim3 g, dim3 b, int64_t nblocks, int r
   return hipGetLastError();
 }
 
-template <class S>
-hipError_t launch_op_t(int op, const Args& a, int U, int64_t nblocks, bool window, const Shape& sh,
-                       hipStream_t st) {
-  const int64_t grid = sh.xcd_remap ? (nblocks + 7) / 8 * 8 : nblocks;
-  const dim3 g((unsigned)grid), b((unsigned)(64 * sh.waves_per_block));
-  if (window) {
-    switch (op) {
-      case OP_GRAD: return launch_win<S, OP_GRAD>(a, U, g, b, nblocks, sh.xcd_remap, st);
-      case OP_DIV: return launch_win<S, OP_DIV>(a, U, g, b, nblocks, sh.xcd_remap, st);
-      case OP_GRADT: return launch_win<S, OP_GRADT>(a, U, g, b, nblocks, sh.xcd_remap, st);
-      case OP_DIVT: return launch_win<S, OP_DIVT>(a, U, g, b, nblocks, sh.xcd_remap, st);
-      default: return hipErrorInvalidValue;
-    }
-  }
-  switch (op) {
-    case OP_GRAD: return launch_u<S, OP_GRAD>(a, U, g, b, nblocks, sh.xcd_remap, st);
-    case OP_DIV: return launch_u<S, OP_DIV>(a, U, g, b, nblocks, sh.xcd_remap, st);
-    case OP_GRADT: return launch_u<S, OP_GRADT>(a, U, g, b, nblocks, sh.xcd_remap, st);
-    case OP_DIVT: return launch_u<S, OP_DIVT>(a, U, g, b, nblocks, sh.xcd_remap, st);
-    case OP_LAP: return launch_u<S, OP_LAP>(a, U, g, b, nblocks, sh.xcd_remap, st);
-    default: return hipErrorInvalidValue;
-  }
-}
-
 template <class S, int OP>
 hipError_t launch_tile_u(const TileArgs& a, int U, dim3 g, dim3 b, uint32_t lds, int64_t nblocks, int remap,
                          hipStream_t st) {
@@ -2510,6 +2494,65 @@ hipError_t launch_tile2_u(const TileArgs& a, int U, dim3 g, dim3 b, uint32_t buf
   return hipGetLastError();
 }
 
+template <class S, int OP, int UMAX>
+hipError_t launch_tb(const TileArgs& a, const BatchTile* tr, const int32_t* pre, int ntr, int32_t* ctr, int32_t claim,
+                     uint32_t lds, int waves, int64_t grid, hipStream_t st) {
+  const void* fn = reinterpret_cast<const void*>(&k_tile_batched<S, OP, UMAX>);
+  if (lds > 65536) {
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  const dim3 g((unsigned)grid), b((unsigned)(64 * waves));
+  hipLaunchKernelGGL((k_tile_batched<S, OP, UMAX>), g, b, lds, st, a, tr, pre, ntr, ctr, claim);
+  return hipGetLastError();
+}
+
+template <class S, int OP>
+const void* tb_fn_u(int umax) {
+  return umax == 1   ? reinterpret_cast<const void*>(&k_tile_batched<S, OP, 1>)
+         : umax == 2 ? reinterpret_cast<const void*>(&k_tile_batched<S, OP, 2>)
+                     : reinterpret_cast<const void*>(&k_tile_batched<S, OP, 3>);
+}
+
+template <class S, int OP>
+hipError_t launch_tb_u(const TileArgs& a, const BatchTile* tr, const int32_t* pre, int ntr, int32_t* ctr,
+                       int32_t claim, uint32_t lds, int waves, int64_t grid, int umax, hipStream_t st) {
+  switch (umax) {
+    case 1: return launch_tb<S, OP, 1>(a, tr, pre, ntr, ctr, claim, lds, waves, grid, st);
+    case 2: return launch_tb<S, OP, 2>(a, tr, pre, ntr, ctr, claim, lds, waves, grid, st);
+    default: return launch_tb<S, OP, 3>(a, tr, pre, ntr, ctr, claim, lds, waves, grid, st);
+  }
+}
+
+}  // namespace
+
+// Launches of one element type, instantiated by a compilation of this file of
+// their own per type (ATLAS_KERNEL_TYPE), so that the types build in parallel.
+
+template <class S>
+hipError_t launch_op_t(int op, const Args& a, int U, int64_t nblocks, bool window, const Shape& sh,
+                       hipStream_t st) {
+  const int64_t grid = sh.xcd_remap ? (nblocks + 7) / 8 * 8 : nblocks;
+  const dim3 g((unsigned)grid), b((unsigned)(64 * sh.waves_per_block));
+  if (window) {
+    switch (op) {
+      case OP_GRAD: return launch_win<S, OP_GRAD>(a, U, g, b, nblocks, sh.xcd_remap, st);
+      case OP_DIV: return launch_win<S, OP_DIV>(a, U, g, b, nblocks, sh.xcd_remap, st);
+      case OP_GRADT: return launch_win<S, OP_GRADT>(a, U, g, b, nblocks, sh.xcd_remap, st);
+      case OP_DIVT: return launch_win<S, OP_DIVT>(a, U, g, b, nblocks, sh.xcd_remap, st);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  switch (op) {
+    case OP_GRAD: return launch_u<S, OP_GRAD>(a, U, g, b, nblocks, sh.xcd_remap, st);
+    case OP_DIV: return launch_u<S, OP_DIV>(a, U, g, b, nblocks, sh.xcd_remap, st);
+    case OP_GRADT: return launch_u<S, OP_GRADT>(a, U, g, b, nblocks, sh.xcd_remap, st);
+    case OP_DIVT: return launch_u<S, OP_DIVT>(a, U, g, b, nblocks, sh.xcd_remap, st);
+    case OP_LAP: return launch_u<S, OP_LAP>(a, U, g, b, nblocks, sh.xcd_remap, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 template <class S>
 hipError_t launch_tiles2_t(int op, const TileArgs& a, int U, uint32_t buf_bytes, uint32_t lds, int nprod, int ncons,
                            int per_cu, int num_cus, int P, const Shape& sh, hipStream_t st) {
@@ -2545,7 +2588,52 @@ hipError_t launch_tiles_t(int op, const TileArgs& a, int U, uint32_t lds, const 
   }
 }
 
-}  // namespace
+template <class S>
+const void* tb_fn(int op, int umax) {
+  switch (op) {
+    case OP_GRAD: return tb_fn_u<S, OP_GRAD>(umax);
+    case OP_DIV: return tb_fn_u<S, OP_DIV>(umax);
+    case OP_GRADT: return tb_fn_u<S, OP_GRADT>(umax);
+    case OP_DIVT: return tb_fn_u<S, OP_DIVT>(umax);
+    case OP_DIVCURL: return tb_fn_u<S, OP_DIVCURL>(umax);
+    default: return nullptr;
+  }
+}
+
+template <class S>
+hipError_t launch_tb_t(int op, const TileArgs& a, const BatchTile* tr, const int32_t* pre, int ntr, int32_t* ctr,
+                       int32_t claim, uint32_t lds, int waves, int64_t grid, int umax, hipStream_t st) {
+  switch (op) {
+    case OP_GRAD: return launch_tb_u<S, OP_GRAD>(a, tr, pre, ntr, ctr, claim, lds, waves, grid, umax, st);
+    case OP_DIV: return launch_tb_u<S, OP_DIV>(a, tr, pre, ntr, ctr, claim, lds, waves, grid, umax, st);
+    case OP_GRADT: return launch_tb_u<S, OP_GRADT>(a, tr, pre, ntr, ctr, claim, lds, waves, grid, umax, st);
+    case OP_DIVT: return launch_tb_u<S, OP_DIVT>(a, tr, pre, ntr, ctr, claim, lds, waves, grid, umax, st);
+    case OP_DIVCURL: return launch_tb_u<S, OP_DIVCURL>(a, tr, pre, ntr, ctr, claim, lds, waves, grid, umax, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+#define ATLAS_FIELD_LAUNCHES(KW, S)                                                                                   \
+  KW template hipError_t launch_op_t<S>(int, const Args&, int, int64_t, bool, const Shape&, hipStream_t);             \
+  KW template hipError_t launch_tiles_t<S>(int, const TileArgs&, int, uint32_t, const Shape&, hipStream_t);
+#define ATLAS_PERSISTENT_LAUNCHES(KW, S)                                                                              \
+  KW template hipError_t launch_tiles2_t<S>(int, const TileArgs&, int, uint32_t, uint32_t, int, int, int, int, int,   \
+                                            const Shape&, hipStream_t);                                               \
+  KW template const void* tb_fn<S>(int, int);                                                                         \
+  KW template hipError_t launch_tb_t<S>(int, const TileArgs&, const BatchTile*, const int32_t*, int, int32_t*,        \
+                                        int32_t, uint32_t, int, int64_t, int, hipStream_t);
+
+#ifdef ATLAS_KERNEL_TYPE
+ATLAS_FIELD_LAUNCHES(, ATLAS_KERNEL_TYPE)
+#ifndef ATLAS_KERNEL_FIELD_ONLY
+ATLAS_PERSISTENT_LAUNCHES(, ATLAS_KERNEL_TYPE)
+#endif
+#else
+ATLAS_FIELD_LAUNCHES(extern, double)
+ATLAS_FIELD_LAUNCHES(extern, float)
+ATLAS_FIELD_LAUNCHES(extern, bf16_t)
+ATLAS_PERSISTENT_LAUNCHES(extern, double)
+ATLAS_PERSISTENT_LAUNCHES(extern, float)
 
 bool uses_window(int op, int nlev, const Shape& sh) {
   return op != OP_LAP && nlev > 32 && sh.row_window != 2;
@@ -2982,65 +3070,6 @@ hipError_t scratch_address(int device, double** ptr) {
   return hipSuccess;
 }
 
-namespace {
-
-template <class S, int OP, int UMAX>
-hipError_t launch_tb(const TileArgs& a, const BatchTile* tr, const int32_t* pre, int ntr, int32_t* ctr, int32_t claim,
-                     uint32_t lds, int waves, int64_t grid, hipStream_t st) {
-  const void* fn = reinterpret_cast<const void*>(&k_tile_batched<S, OP, UMAX>);
-  if (lds > 65536) {
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  const dim3 g((unsigned)grid), b((unsigned)(64 * waves));
-  hipLaunchKernelGGL((k_tile_batched<S, OP, UMAX>), g, b, lds, st, a, tr, pre, ntr, ctr, claim);
-  return hipGetLastError();
-}
-
-template <class S, int OP>
-const void* tb_fn_u(int umax) {
-  return umax == 1   ? reinterpret_cast<const void*>(&k_tile_batched<S, OP, 1>)
-         : umax == 2 ? reinterpret_cast<const void*>(&k_tile_batched<S, OP, 2>)
-                     : reinterpret_cast<const void*>(&k_tile_batched<S, OP, 3>);
-}
-
-template <class S>
-const void* tb_fn(int op, int umax) {
-  switch (op) {
-    case OP_GRAD: return tb_fn_u<S, OP_GRAD>(umax);
-    case OP_DIV: return tb_fn_u<S, OP_DIV>(umax);
-    case OP_GRADT: return tb_fn_u<S, OP_GRADT>(umax);
-    case OP_DIVT: return tb_fn_u<S, OP_DIVT>(umax);
-    case OP_DIVCURL: return tb_fn_u<S, OP_DIVCURL>(umax);
-    default: return nullptr;
-  }
-}
-
-template <class S, int OP>
-hipError_t launch_tb_u(const TileArgs& a, const BatchTile* tr, const int32_t* pre, int ntr, int32_t* ctr,
-                       int32_t claim, uint32_t lds, int waves, int64_t grid, int umax, hipStream_t st) {
-  switch (umax) {
-    case 1: return launch_tb<S, OP, 1>(a, tr, pre, ntr, ctr, claim, lds, waves, grid, st);
-    case 2: return launch_tb<S, OP, 2>(a, tr, pre, ntr, ctr, claim, lds, waves, grid, st);
-    default: return launch_tb<S, OP, 3>(a, tr, pre, ntr, ctr, claim, lds, waves, grid, st);
-  }
-}
-
-template <class S>
-hipError_t launch_tb_t(int op, const TileArgs& a, const BatchTile* tr, const int32_t* pre, int ntr, int32_t* ctr,
-                       int32_t claim, uint32_t lds, int waves, int64_t grid, int umax, hipStream_t st) {
-  switch (op) {
-    case OP_GRAD: return launch_tb_u<S, OP_GRAD>(a, tr, pre, ntr, ctr, claim, lds, waves, grid, umax, st);
-    case OP_DIV: return launch_tb_u<S, OP_DIV>(a, tr, pre, ntr, ctr, claim, lds, waves, grid, umax, st);
-    case OP_GRADT: return launch_tb_u<S, OP_GRADT>(a, tr, pre, ntr, ctr, claim, lds, waves, grid, umax, st);
-    case OP_DIVT: return launch_tb_u<S, OP_DIVT>(a, tr, pre, ntr, ctr, claim, lds, waves, grid, umax, st);
-    case OP_DIVCURL: return launch_tb_u<S, OP_DIVCURL>(a, tr, pre, ntr, ctr, claim, lds, waves, grid, umax, st);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-}  // namespace
-
 int tiles_batched_per_cu(int op, int dtype, uint32_t lds, int waves, int umax) {
   const int kop = kernel_op(op);
   const void* fn = dtype == DT_F64 ? tb_fn<double>(kop, umax) : dtype == DT_F32 ? tb_fn<float>(kop, umax) : nullptr;
@@ -3108,5 +3137,7 @@ hipError_t launch_remap_adjoint(int dtype, const int64_t* off, const int32_t* tt
     default: return hipErrorInvalidValue;
   }
 }
+
+#endif  // ATLAS_KERNEL_TYPE
 
 }  // namespace atlasnabla
