@@ -134,12 +134,15 @@ struct atlas_mesh_s {
     group_blocks(host_nbr, g.block, ht, nblk);
     // with the tiles' block counts above their column counts, and their
     // segment counts above their node counts
-    std::vector<int32_t> info = ht.info;
+    std::vector<int32_t> info = ht.info, sched;
     for (int64_t t = 0; t < ht.ntiles; ++t) {
       info[4 * t + 2] |= nblk[t] << 16;
       info[4 * t + 3] |= (ht.info[4 * t + 4] - ht.info[4 * t]) << 16;
     }
+    schedule_tiles(host, ht, info, h, sched);
     dt.info = upload(info);
+    dt.sched = upload(sched);
+    dt.nsched = (int64_t)sched.size() / 4;
     dt.segs = upload(ht.segs);
     dt.order = upload(ht.order);
     dt.loc = upload(ht.loc);
@@ -250,7 +253,7 @@ void shape_out(const Shape& s, atlas_tune_t* t) {
   t->waves_per_block = s.waves_per_block;
   t->nodes_per_wave = s.nodes_per_wave;
   t->blocks_per_cu = s.blocks_per_cu;
-  t->xcd_remap = s.xcd_remap < 0 ? 0 : s.xcd_remap ? 1 : 2;
+  t->xcd_remap = s.xcd_remap < 0 || s.xcd_remap == kXcdSchedule ? 0 : s.xcd_remap ? 1 : 2;   // 0: the library's own
   t->lanes_per_node = s.lanes_per_node;
   t->slices_per_iter = s.slices_per_iter;
   t->band_rows = s.band_rows;

@@ -1566,10 +1566,21 @@ __device__ __forceinline__ void tile_work(const TileArgs& a, int64_t tile, int c
 template <class S, int OP, int U>
 __global__ __launch_bounds__((kTileThreads<S, OP, U>), (kTileMinWaves<S, OP, U>)) void k_tile(TileArgs a, int64_t nblocks, int remap) {
   extern __shared__ __align__(16) char lds[];
-  const int64_t lb = logical_block(blockIdx.x, nblocks, remap);
-  if (lb >= nblocks) return;
-  const int64_t tile = lb / a.nchunks;
-  const int chunk = (int)(lb - tile * a.nchunks);
+  int64_t tile;
+  int chunk;
+  if (remap == kXcdSchedule) {
+    // entry 8 i + x of the schedule is XCD x's i-th tile (or a hole)
+    const int64_t q = blockIdx.x >> 3;
+    const int64_t i = a.nchunks == 1 ? q : q / a.nchunks;
+    chunk = (int)(q - i * a.nchunks);
+    tile = 8 * i + (blockIdx.x & 7);
+    if ((ld_uniform(a.info + 4 * tile + 3) & 0xffff) == 0) return;
+  } else {
+    const int64_t lb = logical_block(blockIdx.x, nblocks, remap);
+    if (lb >= nblocks) return;
+    tile = lb / a.nchunks;
+    chunk = (int)(lb - tile * a.nchunks);
+  }
   const int W = blockDim.x >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
@@ -2573,8 +2584,8 @@ hipError_t launch_tiles2_t(int op, const TileArgs& a, int U, uint32_t buf_bytes,
 
 template <class S>
 hipError_t launch_tiles_t(int op, const TileArgs& a, int U, uint32_t lds, const Shape& sh, hipStream_t st) {
-  const int64_t nblocks = a.ntiles * a.nchunks;
-  const int64_t grid = sh.xcd_remap ? (nblocks + 7) / 8 * 8 : nblocks;
+  const int64_t nblocks = a.ntiles * a.nchunks;   // scheduled tiles: a multiple of 8
+  const int64_t grid = sh.xcd_remap == 1 ? (nblocks + 7) / 8 * 8 : nblocks;
   const dim3 g((unsigned)grid), b((unsigned)(64 * sh.waves_per_block));
   switch (op) {
     case OP_GRAD: return launch_tile_u<S, OP_GRAD>(a, U, g, b, lds, nblocks, sh.xcd_remap, st);
@@ -2737,31 +2748,41 @@ Shape resolve_path(int op, int dtype, int nlev, const Shape& sh) {
   // FP64 one-pass gradient and Laplacian: one slice per step fits 16 waves
   // in 128 registers (7.1 ms against 7.7 ms with two slices and 8 waves)
   if (op == OP_GRADLAP && dtype == DT_F64 && !e.slices_per_iter) e.slices_per_iter = 1;
-  // One band of rows at a time, swept whole along the latitude circle (see
-  // resolve_shape); the FP64 one-pass gradient and Laplacian, whose halo is
-  // the widest, does better with eight bands side by side (O640 x 137: 1.83
-  // ms against 1.88, O320 0.47 against 0.50).
-  if (!e.run_nodes && !(op == OP_GRADLAP && dtype == DT_F64)) e.run_nodes = 1;
+  // one band of rows at a time, around the whole latitude circle (see
+  // resolve_shape)
+  if (!e.run_nodes) e.run_nodes = 1;
   return e;
 }
 
 }  // namespace
 
 // Order of the work over the XCDs, where the caller does not fix it.  The
-// one-tile form takes its tiles in plain order, so the tiles in flight on
-// the whole GPU lie side by side along a few rows and their reads and writes
-// fall into few DRAM pages; the halo rows come from the 256 MiB cache behind
-// the L2s when they have left an XCD's own.  A contiguous eighth of the order
-// per XCD keeps halo rows in its L2 but has eight times as many rows open:
-// a plain kernel reading 1 and writing 2 bytes over rows visited that way
-// drops from 6.3 to 5.1 TB/s.  O640 x 137 FP32, eighths of 8-band sweeps ->
-// plain order of single bands: gradient 614 -> 552 us, divergence 647 -> 602,
-// Laplacian 657 -> 630, gradient and Laplacian 994 -> 936, divergence and
-// curl 859 -> 806; O1280 gradient 2.41 -> 2.22 ms; BF16 and FP64 4-13 %.
+// one-tile form goes around one band of rows at a time, so the tiles in
+// flight on the whole GPU lie side by side along a few rows and their reads
+// and writes fall into few DRAM pages; halo rows come from the 256 MiB cache
+// behind the L2s when they have left an XCD's own.  A contiguous eighth of
+// the order per XCD keeps halo rows in its L2 but has eight times as many
+// rows open: a plain kernel reading 1 and writing 2 bytes over rows visited
+// that way drops from 6.3 to 5.1 TB/s.  O640 x 137 FP32, eighths of 8-band
+// sweeps -> plain order of single bands: gradient 614 -> 552 us, divergence
+// 647 -> 602, Laplacian 657 -> 630, gradient and Laplacian 994 -> 936,
+// divergence and curl 859 -> 806; O1280 gradient 2.41 -> 2.22 ms; BF16 and
+// FP64 4-13 %.
+// Within a band each XCD takes an eighth of the longitude (schedule_tiles),
+// so tiles side by side share their halo columns in one L2, where that halo
+// is wide: two columns each side (the two-ring operators: FP32 Laplacian 580
+// -> 553 us, gradient and Laplacian 915 -> 872, FP64 1.88 -> 1.84 ms) or two
+// components (divergence 599 -> 571 us FP32, 1.35 -> 1.31 ms FP64).  The
+// scalar-input 1-ring operators lose by it (FP64 gradient 1.10 -> 1.15 ms), so
+// do most BF16 columns, half as wide (gradient 330 -> 344 us, divergence and
+// curl 368 -> 382 at 91 levels): they keep the plain order.
 // The other paths, without a tile's reuse of its own halo, keep the eighths.
 Shape resolve_shape(int op, int dtype, int nlev, const Shape& sh) {
   Shape e = resolve_path(op, dtype, nlev, sh);
-  if (e.xcd_remap < 0) e.xcd_remap = e.lds_tiles == 3 && uses_tiles(op, dtype, nlev, e) ? 0 : 1;
+  if (e.xcd_remap >= 0) return e;
+  const int k = kernel_op(op);
+  if (!(e.lds_tiles == 3 && uses_tiles(op, dtype, nlev, e))) e.xcd_remap = 1;
+  else e.xcd_remap = k == OP_GRAD || k == OP_DIVT || dtype == DT_BF16 ? 0 : kXcdSchedule;
   return e;
 }
 
@@ -2936,6 +2957,10 @@ hipError_t launch_tiles(int op, int dtype, const DevTiles& dt, const void* rec, 
   if (two != (out2 != nullptr) || (two && shape.lds_tiles != 3))
     return hipErrorInvalidValue;   // the one-pass forms: one-tile workgroups, both outputs
   a.ntiles = dt.ntiles;
+  if (shape.lds_tiles == 3 && shape.xcd_remap == kXcdSchedule) {
+    a.info = dt.sched;
+    a.ntiles = dt.nsched;
+  }
   a.L = nlev;
   a.KL = dt.KL;
   a.nchunks = dt.nchunks;

@@ -42,7 +42,8 @@ struct Shape {
   int waves_per_block = 4;   // 64-lane waves per workgroup
   int nodes_per_wave = 1;    // node groups per wave per workgroup
   int blocks_per_cu = 4;     // persistent kernels only
-  int xcd_remap = -1;        // 1: a contiguous part of the work per XCD, 0: plain order; -1: resolve_shape picks
+  int xcd_remap = -1;        // 1: a contiguous part of the work per XCD, 0: plain order, kXcdSchedule: the
+                             // tiling's schedule (one-tile form only); -1: resolve_shape picks
   int lanes_per_node = 0;    // 0: chosen from nlev; else 16, 32 or 64 (nlev > 32)
   int slices_per_iter = 0;   // 0: 3 (capped by the slice count); else 1..3
   int band_rows = 0;         // 0: kDefaultBandRows; rows per band of the node order
@@ -61,6 +62,7 @@ struct Shape {
   int batch_claim = 0;       // batched persistent form: tiles per work claim (0: kDefaultBatchClaim)
 };
 
+constexpr int kXcdSchedule = 2;
 constexpr int kDefaultBandRows = 32;
 constexpr int kDefaultRunNodes = 16;
 constexpr int kDefaultWindowRunNodes = 64;
@@ -94,6 +96,8 @@ int window_slices(int nlev, const Shape& sh);
 // LDS tile path: device tiles of one tiling (see HaloTiles in mesh.hpp).
 struct DevTiles {
   const int32_t* info = nullptr;
+  const int32_t* sched = nullptr;   // info by XCD, see schedule_tiles
+  int64_t nsched = 0;               // its entries (a multiple of 8)
   const int32_t* segs = nullptr;
   const int32_t* order = nullptr;   // [V] nodes in tile order
   const uint16_t* loc = nullptr;    // [V][8 or 24] LDS positions (source of the records)

@@ -140,6 +140,12 @@ void build_halo_tiles(const HostMesh& m, const OpTables& t, int ring, int band_r
 // order); nblk[t] is the number of blocks of tile t.
 void group_blocks(const OpTables& t, int block_nodes, HaloTiles& ht, std::vector<int32_t>& nblk);
 
+// Tiles by XCD: entry 8 i + x of sched (four int32 each, copied from info) is
+// the i-th tile XCD x takes; entries of zeros are holes.  Band by band, each
+// XCD takes an eighth of the band's tiles, side by side in longitude.
+void schedule_tiles(const HostMesh& m, const HaloTiles& ht, const std::vector<int32_t>& info, int band_rows,
+                    std::vector<int32_t>& sched);
+
 // Remapping from an O-grid mesh to the points of a target grid by linear
 // interpolation over the source triangles in 3-D on the sphere (see
 // remap_build.cpp): per target point the three nodes of the triangle its ray

@@ -814,4 +814,23 @@ void group_blocks(const OpTables& t, int block_nodes, HaloTiles& ht, std::vector
   }
 }
 
+void schedule_tiles(const HostMesh& m, const HaloTiles& ht, const std::vector<int32_t>& info, int band_rows,
+                    std::vector<int32_t>& sched) {
+  if (band_rows < 1) throw std::runtime_error("band_rows must be >= 1");
+  constexpr int64_t kXcds = 8;
+  // tiles of each band, in their order along the band
+  std::vector<std::vector<int64_t>> band((m.nrows + band_rows - 1) / band_rows);
+  for (int64_t t = 0; t < ht.ntiles; ++t)
+    band[m.node_row[ht.order[ht.info[4 * t + 1]]] / band_rows].push_back(t);
+  sched.clear();
+  for (const auto& b : band) {
+    const int64_t n = (int64_t)b.size();
+    for (int64_t i = 0; i < (n + kXcds - 1) / kXcds; ++i)
+      for (int64_t x = 0; x < kXcds; ++x) {
+        const int64_t t = n * x / kXcds + i;
+        for (int q = 0; q < 4; ++q) sched.push_back(t < n * (x + 1) / kXcds ? info[4 * b[t] + q] : 0);
+      }
+  }
+}
+
 }  // namespace atlasnabla
