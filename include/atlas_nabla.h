@@ -163,7 +163,8 @@ int atlas_nabla_laplacian(atlas_mesh_t mesh, int dtype, int32_t nlev,
  * [V][nlev]; grad: vector [V][nlev][2]; lap: scalar [V][nlev]; no two of
  * them may overlap.  Runs as one kernel on the Laplacian's launch shape
  * when that is the one-tile LDS form (the default for columns of more than
- * 32 levels), else as the two calls one after the other. */
+ * 32 levels, and from 8 levels up for fields of at least 2.6 million values
+ * per component), else as the two calls one after the other. */
 int atlas_nabla_gradient_laplacian(atlas_mesh_t mesh, int dtype, int32_t nlev,
                                    const void* f, void* grad, void* lap, void* stream);
 
@@ -193,8 +194,8 @@ int atlas_nabla_curl(atlas_mesh_t mesh, int dtype, int32_t nlev,
  * the sign of zero); the field is read from memory once.  uv: vector
  * [V][nlev][2]; div, zeta: scalar [V][nlev]; no two of them may overlap.
  * One kernel on the divergence's launch shape when that is the one-tile LDS
- * form (the default for columns of more than 32 levels), else the two calls
- * one after the other. */
+ * form (the default for columns of more than 32 levels, and for large fields
+ * from 8 levels up), else the two calls one after the other. */
 int atlas_nabla_divergence_curl(atlas_mesh_t mesh, int dtype, int32_t nlev,
                                 const void* uv, void* div, void* zeta, void* stream);
 
@@ -206,7 +207,8 @@ int atlas_nabla_divergence_curl(atlas_mesh_t mesh, int dtype, int32_t nlev,
  * memory once.  uv: vector [V][nlev][2]; div, fbar: scalar [V][nlev]; no
  * two of them may overlap.  One kernel on the divergence's launch shape
  * when that is the one-tile LDS form (the default for columns of more than
- * 32 levels), else the two calls one after the other. */
+ * 32 levels, and for large fields from 8 levels up), else the two calls one
+ * after the other. */
 int atlas_nabla_divergence_gradient_adjoint(atlas_mesh_t mesh, int dtype, int32_t nlev,
                                             const void* uv, void* div, void* fbar, void* stream);
 
@@ -326,8 +328,10 @@ typedef struct {
   int32_t blocks_per_cu;    /* persistent grid = blocks_per_cu * CU count     */
   int32_t xcd_remap;        /* 1: each XCD walks a contiguous part of the
                                node order (the default, but for one-tile
-                               LDS workgroups), 2: plain order (their
-                               default)                                      */
+                               LDS workgroups), 2: plain order; one-tile
+                               LDS workgroups default to plain order or, per
+                               operator, to an eighth of each band's
+                               longitude per XCD                              */
   int32_t lanes_per_node;   /* 16, 32 or 64 lanes share a column (nlev > 32);
                                columns of <= 32 levels always use nlev lanes */
   int32_t slices_per_iter;  /* level slices in flight per lane, 1..3         */
@@ -345,11 +349,14 @@ typedef struct {
                                levels: 1 walk rows reusing the previous
                                node's column loads (the default), 2 gather
                                every slot per node                            */
-  int32_t lds_tiles;        /* FP32/FP64 columns of more than 32 levels:
-                               stage tiles of nodes with the columns their
-                               stencils read in LDS: 1 persistent workgroups,
-                               double buffered; 3 one tile per workgroup;
-                               0/2 off (the default)                          */
+  int32_t lds_tiles;        /* columns of more than 32 levels: stage tiles of
+                               nodes with the columns their stencils read in
+                               LDS: 1 persistent workgroups, double buffered
+                               (not BF16); 3 one tile per workgroup; 2 off;
+                               0 the library's own, which also takes 3 for
+                               columns of 8 to 32 levels of a field of at
+                               least 5 x 2^19 nodes x levels, if the shape
+                               sets no parameter of the other paths           */
   int32_t tile_kb;          /* LDS budget of one tile in KiB, 8..160 (0: per-
                                operator default); the persistent form holds
                                two tiles, which must fit the CU's 160 KiB     */

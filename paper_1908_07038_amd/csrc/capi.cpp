@@ -89,7 +89,10 @@ struct atlas_mesh_s {
     void* p = nullptr;
     const size_t bytes = v.size() * sizeof(T);
     hipError_t e = hipMalloc(&p, bytes ? bytes : 16);
-    if (e != hipSuccess) throw std::bad_alloc();
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      throw std::bad_alloc();
+    }
     allocations.push_back(p);
     if (bytes) {
       e = hipMemcpy(p, v.data(), bytes, hipMemcpyHostToDevice);
@@ -117,11 +120,17 @@ struct atlas_mesh_s {
     return no;
   }
 
-  // Device tiles of an LDS-tiled launch, built and uploaded on first use.
-  DevTiles tiles(const TileGeom& g, const Shape& sh) {
+  // What a tiling is built from.
+  static std::vector<int64_t> tile_key(const TileGeom& g, const Shape& sh) {
     const int h = sh.band_rows > 0 ? sh.band_rows : kDefaultTileRows;
     const int sweep = sh.run_nodes > 0 ? sh.run_nodes : kDefaultTileSweep;
-    const std::vector<int64_t> key = {g.ring, h, sweep, g.col_bytes, g.row_bytes, g.budget, g.block};
+    return {g.ring, h, sweep, g.col_bytes, g.row_bytes, g.budget, g.block};
+  }
+
+  // Device tiles of an LDS-tiled launch, built and uploaded on first use.
+  DevTiles tiles(const TileGeom& g, const Shape& sh) {
+    const std::vector<int64_t> key = tile_key(g, sh);
+    const int h = (int)key[1], sweep = (int)key[2];
     std::lock_guard<std::mutex> lk(order_mu);
     auto it = tilings.find(key);
     if (it != tilings.end()) return it->second;
@@ -161,9 +170,8 @@ struct atlas_mesh_s {
   // use (one allocation of V records, kept until the mesh is freed).
   const void* tile_records(const TileGeom& g, const Shape& sh, const DevTiles& dt, int op, int dtype,
                            hipStream_t stream) {
-    const int h = sh.band_rows > 0 ? sh.band_rows : kDefaultTileRows;
-    const int sweep = sh.run_nodes > 0 ? sh.run_nodes : kDefaultTileSweep;
-    const std::vector<int64_t> key = {g.ring, h, sweep, g.col_bytes, g.row_bytes, g.budget, g.block, op, dtype};
+    std::vector<int64_t> key = tile_key(g, sh);
+    key.insert(key.end(), {op, dtype});
     std::lock_guard<std::mutex> lk(order_mu);
     auto it = records.find(key);
     if (it != records.end()) return it->second;
@@ -179,6 +187,14 @@ struct atlas_mesh_s {
     if (e != hipSuccess) throw std::runtime_error(std::string("packing tile records: ") + hipGetErrorString(e));
     records[key] = p;
     return p;
+  }
+
+  // Whether a tiling and its node records are there already.
+  bool tiles_ready(const TileGeom& g, const Shape& sh, int op, int dtype) {
+    std::vector<int64_t> key = tile_key(g, sh);
+    key.insert(key.end(), {op, dtype});
+    std::lock_guard<std::mutex> lk(order_mu);
+    return records.count(key) > 0;
   }
 };
 
@@ -324,6 +340,36 @@ int check_shape(Shape& s, const atlas_tune_t* t) {
   return ATLAS_OK;
 }
 
+// The tiles and node records of a call on LDS tiles (tg.KL > 0), built on
+// first use.  tg.KL = 0 on return: the call runs without them -- short columns
+// whose tiles cannot be built now (the stream is being captured, where
+// nothing can be allocated, or memory is short), for which the gather needs
+// nothing of its own.
+int call_tiles(atlas_mesh_t mesh, int op, int dtype, TileGeom& tg, const Shape& sh, DevTiles& dt, const void*& rec,
+               hipStream_t stream) {
+  if (sh.short_tiles && !mesh->tiles_ready(tg, sh, op, dtype)) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) (void)hipGetLastError();
+    if (st != hipStreamCaptureStatusNone) {
+      tg.KL = 0;
+      return ATLAS_OK;
+    }
+  }
+  try {
+    // tilings depend on the byte sizes only; the level chunk is the call's
+    dt = mesh->tiles(tg, sh);
+    dt.KL = tg.KL;
+    dt.nchunks = tg.nchunks;
+    rec = mesh->tile_records(tg, sh, dt, op, dtype, stream);
+  } catch (const std::bad_alloc&) {
+    if (!sh.short_tiles) return fail(ATLAS_ENOMEM, "cannot allocate the LDS tiles");
+    tg.KL = 0;
+  } catch (const std::exception& ex) {
+    return fail(ATLAS_EHIP, ex.what());
+  }
+  return ATLAS_OK;
+}
+
 int run_op(atlas_mesh_t mesh, int op, int dtype, int32_t nlev, const void* in, void* out, void* stream,
            const Shape* shape_override = nullptr) {
   int rc = check_mesh_device(mesh);
@@ -342,31 +388,26 @@ int run_op(atlas_mesh_t mesh, int op, int dtype, int32_t nlev, const void* in, v
   DeviceGuard g(mesh->device);
   if (!g.ok) return fail(ATLAS_EHIP, "cannot select the mesh's device");
   const Shape& asked = shape_override ? *shape_override : mesh->shape[op][dtype];
-  Shape sh = resolve_shape(op, dtype, nlev, asked);
+  Shape sh = resolve_shape(op, dtype, nlev, V, asked);
   TileGeom tg = uses_tiles(op, dtype, nlev, sh) ? tile_geom(op, dtype, nlev, sh) : TileGeom();
   // BF16 tiles copy whole dwords around each column segment: they need a
   // 4-byte aligned field (else the row-window walk or gather runs)
   if (dtype == ATLAS_BF16 && ((uintptr_t)in & 3u)) tg.KL = 0;
-  if (tg.KL > 0) {   // tiles asked for and a tile geometry fits the budget
-    DevTiles dt;
-    const void* rec = nullptr;
-    try {
-      // tilings depend on the byte sizes only; the level chunk is the call's
-      dt = mesh->tiles(tg, sh);
-      dt.KL = tg.KL;
-      dt.nchunks = tg.nchunks;
-      rec = mesh->tile_records(tg, sh, dt, op, dtype, (hipStream_t)stream);
-    } catch (const std::bad_alloc&) {
-      return fail(ATLAS_ENOMEM, "cannot allocate the LDS tiles");
-    } catch (const std::exception& ex) {
-      return fail(ATLAS_EHIP, ex.what());
-    }
+  DevTiles dt;
+  const void* rec = nullptr;
+  // tiles asked for and a tile geometry fits the budget
+  if (tg.KL > 0 && (rc = call_tiles(mesh, op, dtype, tg, sh, dt, rec, (hipStream_t)stream))) return rc;
+  if (tg.KL > 0) {
     hipError_t e = launch_tiles(op, dtype, dt, rec, nlev, in, out, sh, mesh->num_cus, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, kOpName[op]);
     return ATLAS_OK;
   }
   // no tiles: their order's defaults do not apply; the row-window walk works
   // best on long runs
+  if (sh.short_tiles) {
+    sh = asked;
+    sh.lds_tiles = 2;
+  }
   sh.run_nodes = asked.run_nodes;
   if (asked.xcd_remap < 0) sh.xcd_remap = 1;
   if (sh.run_nodes == 0 && uses_window(op, nlev, sh)) sh.run_nodes = kDefaultWindowRunNodes;
@@ -567,23 +608,14 @@ int atlas_nabla_gradient_laplacian(atlas_mesh_t mesh, int dtype, int32_t nlev, c
   if (!g.ok) return fail(ATLAS_EHIP, "cannot select the mesh's device");
   // the fused pass runs on the Laplacian's launch shape when that is the
   // one-tile LDS form; otherwise the two operators run one after the other
-  const Shape sh = resolve_shape(OP_GRADLAP, dtype, nlev, mesh->shape[OP_LAP][dtype]);
+  const Shape sh = resolve_shape(OP_GRADLAP, dtype, nlev, V, mesh->shape[OP_LAP][dtype]);
   TileGeom tg;
   if (sh.lds_tiles == 3 && uses_tiles(OP_GRADLAP, dtype, nlev, sh)) tg = tile_geom(OP_GRADLAP, dtype, nlev, sh);
   if (dtype == ATLAS_BF16 && ((uintptr_t)f & 3u)) tg.KL = 0;
+  DevTiles dt;
+  const void* rec = nullptr;
+  if (tg.KL > 0 && (rc = call_tiles(mesh, OP_GRADLAP, dtype, tg, sh, dt, rec, (hipStream_t)stream))) return rc;
   if (tg.KL > 0) {
-    DevTiles dt;
-    const void* rec = nullptr;
-    try {
-      dt = mesh->tiles(tg, sh);
-      dt.KL = tg.KL;
-      dt.nchunks = tg.nchunks;
-      rec = mesh->tile_records(tg, sh, dt, OP_GRADLAP, dtype, (hipStream_t)stream);
-    } catch (const std::bad_alloc&) {
-      return fail(ATLAS_ENOMEM, "cannot allocate the LDS tiles");
-    } catch (const std::exception& ex) {
-      return fail(ATLAS_EHIP, ex.what());
-    }
     hipError_t e = launch_tiles(OP_GRADLAP, dtype, dt, rec, nlev, f, lap, sh, mesh->num_cus, (hipStream_t)stream, grad);
     if (e != hipSuccess) return hip_fail(e, "gradient_laplacian");
     return ATLAS_OK;
@@ -616,23 +648,14 @@ int divergence_pair(atlas_mesh_t mesh, int fused, int op2, const char* name, int
                                   " must not overlap");
   DeviceGuard g(mesh->device);
   if (!g.ok) return fail(ATLAS_EHIP, "cannot select the mesh's device");
-  const Shape sh = resolve_shape(fused, dtype, nlev, mesh->shape[OP_DIV][dtype]);
+  const Shape sh = resolve_shape(fused, dtype, nlev, V, mesh->shape[OP_DIV][dtype]);
   TileGeom tg;
   if (sh.lds_tiles == 3 && uses_tiles(fused, dtype, nlev, sh)) tg = tile_geom(fused, dtype, nlev, sh);
   if (dtype == ATLAS_BF16 && ((uintptr_t)uv & 3u)) tg.KL = 0;
+  DevTiles dt;
+  const void* rec = nullptr;
+  if (tg.KL > 0 && (rc = call_tiles(mesh, fused, dtype, tg, sh, dt, rec, (hipStream_t)stream))) return rc;
   if (tg.KL > 0) {
-    DevTiles dt;
-    const void* rec = nullptr;
-    try {
-      dt = mesh->tiles(tg, sh);
-      dt.KL = tg.KL;
-      dt.nchunks = tg.nchunks;
-      rec = mesh->tile_records(tg, sh, dt, fused, dtype, (hipStream_t)stream);
-    } catch (const std::bad_alloc&) {
-      return fail(ATLAS_ENOMEM, "cannot allocate the LDS tiles");
-    } catch (const std::exception& ex) {
-      return fail(ATLAS_EHIP, ex.what());
-    }
     hipError_t e = launch_tiles(fused, dtype, dt, rec, nlev, uv, div, sh, mesh->num_cus, (hipStream_t)stream, out2);
     if (e != hipSuccess) return hip_fail(e, name);
     return ATLAS_OK;
@@ -918,7 +941,7 @@ int atlas_nabla_describe(atlas_mesh_t mesh, int dtype, uint32_t op, int32_t nlev
   if (nlev <= 0) return fail(ATLAS_ESHAPE, "nlev must be >= 1");
   if (kernel && len <= 0) return fail(ATLAS_EINVAL, "len must be positive");
   const int k = fused >= 0 ? fused : o;
-  const Shape sh = resolve_shape(k, dtype, nlev, mesh->shape[o][dtype]);
+  const Shape sh = resolve_shape(k, dtype, nlev, mesh->host.V, mesh->shape[o][dtype]);
   if (resolved) shape_out(sh, resolved);
   if (kernel) {
     // the one-pass calls run their kernel on the one-tile form only
@@ -1017,12 +1040,13 @@ int atlas_nabla_tune(atlas_mesh_t mesh, int dtype, uint32_t op, int32_t nlev, co
           }
     }
   }
-  if (bs.lds_tiles == 1 || bs.lds_tiles == 3 || (bs.lds_tiles == 0 && uses_tiles(o, dtype, nlev,
-                                                                                 resolve_shape(o, dtype, nlev, bs)))) {
-    // LDS tiles won: bands swept together
-    const Shape base = resolve_shape(o, dtype, nlev, bs);
+  if (bs.lds_tiles == 1 || bs.lds_tiles == 3 ||
+      (bs.lds_tiles == 0 && uses_tiles(o, dtype, nlev, resolve_shape(o, dtype, nlev, mesh->host.V, bs)))) {
+    // LDS tiles won: bands swept together (short columns: the default's only)
+    const Shape base = resolve_shape(o, dtype, nlev, mesh->host.V, bs);
     const int sweeps[] = {4, 8, 16};
     for (int b : sweeps) {
+      if (nlev <= 32) break;
       Shape s = base;
       s.run_nodes = b;
       if ((rc = time_shape(s))) goto done;
@@ -1151,7 +1175,7 @@ int plan_op(atlas_batch_s* b, int o, BatchOp& bo, bool pair = false) {
   int Lmax = 1;
   for (const atlas_tracer_desc_t& d : b->descs) Lmax = std::max(Lmax, d.nlev);
   // tile defaults of the long-column launch, also for batches of short columns
-  Shape sh = resolve_shape(k, b->dtype, std::max(Lmax, 33), b->shape[o]);
+  Shape sh = resolve_shape(k, b->dtype, std::max(Lmax, 33), b->mesh->host.V, b->shape[o]);
   sh.run_nodes = b->shape[o].run_nodes;   // each XCD walks a share of its own: the default sweep keeps its halo rows in L2
   if (sh.lds_tiles != 3) return ATLAS_OK;
   const int ntr = (int)b->descs.size();

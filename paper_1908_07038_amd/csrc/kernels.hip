@@ -1486,6 +1486,117 @@ __device__ __forceinline__ void tile_tail(const TileArgs& a, const char* lds, in
   }
 }
 
+// Blocks of a tile of short columns (rem <= 32 levels in all): G = 64 / rem
+// blocks share a wave, lane = (block tj, level tt), each lane with its block's
+// row positions and table rows.  As tile_block, the columns the block's nodes
+// share are read once; table rows come per lane from LDS.  Bound by LDS reads
+// and, FP32 at O640 x 19, by memory: gradient 102 us (4.5 TB/s over the
+// arrays), Laplacian 124.
+template <class S, int OP, int NB>
+__device__ __forceinline__ void tile_short(const TileArgs& a, const char* lds, int32_t nblk, uint32_t data_off,
+                                           uint32_t colB, int k0, int rem, int tj, int tt, int wave, int W) {
+  using R = TileRec<S, OP>;
+  using C = typename Traits<S>::C;
+  using C2 = typename Traits<S>::C2;
+  using X = typename WinT<S, R::kRing2 ? (int)OP_GRAD : OP>::X;
+  constexpr uint32_t kEl = (uint32_t)sizeof(S) * R::kCin;
+  constexpr uint32_t kOut = (OP == OP_GRAD || OP == OP_DIVT) ? 2 : 1;
+  constexpr int ring = R::kRing2 ? 2 : 1;
+  const int G = 64 / rem;
+  for (int32_t g0 = wave * G; g0 < nblk; g0 += W * G) {
+    const bool ok = tj < G && g0 + tj < nblk;
+    const uint32_t ro = (uint32_t)((ok ? g0 + tj : g0) * NB) * R::kBytes;
+    auto at = [&](int s) -> uint32_t {
+      uint32_t p = lds_ld<uint16_t>(lds, ro + R::kCoefB + 2 * s);
+      if (s == R::kEntries - 1) p &= (1u << kLocCountShift) - 1;
+      if constexpr (sizeof(S) == 2) return lds_ld<uint32_t>(lds, data_off + 4 * p) + (uint32_t)tt * kEl;
+      else return data_off + p * colB + (uint32_t)tt * kEl;
+    };
+    uint32_t row[2 * ring + 1];   // column 0 of the rows, the nodes' own at ring
+    row[ring] = at(R::kEntries - 1);
+    row[ring - 1] = at(0);
+    row[ring + 1] = at(4);
+    if constexpr (R::kRing2) {
+      row[0] = at(6);
+      row[4] = at(15);
+    }
+    auto get = [&](int r, int x) -> X { return lds_elem<S, X>(lds, row[r] + (uint32_t)x * colB); };
+    const uint32_t o0 = (uint32_t)lds_ld<int32_t>(lds, ro + R::kIdOff) * (uint32_t)a.L + (uint32_t)(k0 + tt);
+    if constexpr (!R::kRing2) {
+      X up[NB + 1], mi[NB + 2], dn[NB + 1];
+#pragma unroll
+      for (int x = 0; x < NB + 1; ++x) up[x] = get(0, x);
+#pragma unroll
+      for (int x = 0; x < NB + 2; ++x) mi[x] = get(1, x - 1);
+#pragma unroll
+      for (int x = 0; x < NB + 1; ++x) dn[x] = get(2, x);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const uint32_t rc = ro + (uint32_t)b * R::kBytes;
+        const X v[6] = {up[b], up[b + 1], mi[b], mi[b + 2], dn[b], dn[b + 1]};
+        auto combine = [&](uint32_t cb, C& r0, C& r1) {
+          C2 cf[6], dg = {0, 0};
+#pragma unroll
+          for (int q = 0; q < 6; ++q) cf[q] = lds_ld<C2>(lds, rc + cb + q * (uint32_t)sizeof(C2));
+          if constexpr (OP != OP_GRAD) dg = lds_ld<C2>(lds, rc + cb + 7 * (uint32_t)sizeof(C2));
+          win_combine<S, OP, 6>(mi[b + 1], v, cf, dg, r0, r1);
+        };
+        C r0, r1, z0, unused;
+        combine(0, r0, r1);
+        if constexpr (R::kDual) combine(8 * (uint32_t)sizeof(C2), z0, unused);
+        if (ok) {
+          const size_t o = (size_t)(o0 + (uint32_t)(b * a.L));
+          win_store<S, OP>(static_cast<S*>(a.out) + kOut * o, 0, a.nt, r0, r1);
+          if constexpr (R::kDual) win_store<S, OP>(static_cast<S*>(a.out2) + o, 0, a.nt, z0, 0);
+        }
+      }
+    } else {
+      C t2[NB + 2], up[NB + 3], mi[NB + 4], dn[NB + 3], bb[NB + 2];
+#pragma unroll
+      for (int x = 0; x < NB + 2; ++x) t2[x] = get(0, x);
+#pragma unroll
+      for (int x = 0; x < NB + 3; ++x) up[x] = get(1, x - 1);
+#pragma unroll
+      for (int x = 0; x < NB + 4; ++x) mi[x] = get(2, x - 2);
+#pragma unroll
+      for (int x = 0; x < NB + 3; ++x) dn[x] = get(3, x - 1);
+#pragma unroll
+      for (int x = 0; x < NB + 2; ++x) bb[x] = get(4, x);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const uint32_t rc = ro + (uint32_t)b * R::kBytes;
+        const C v[18] = {up[b + 1], up[b + 2], mi[b + 1], mi[b + 3], dn[b + 1], dn[b + 2],
+                         t2[b], t2[b + 1], t2[b + 2], up[b], up[b + 3], mi[b], mi[b + 4],
+                         dn[b], dn[b + 3], bb[b], bb[b + 1], bb[b + 2]};
+        C ac = 0, ax = 0, ay = 0;
+#pragma unroll
+        for (int q = 0; q < 18; ++q) {
+          const C d = v[q] - mi[b + 2];
+          ac = fma(lds_ld<C>(lds, rc + q * (uint32_t)sizeof(C)), d, ac);
+          if constexpr (R::kGrad) {
+            if (q < 6) {
+              const C2 cq = lds_ld<C2>(lds, rc + R::kLapB + q * (uint32_t)sizeof(C2));
+              ax = fma(cq.x, d, ax);
+              ay = fma(cq.y, d, ay);
+            }
+          }
+        }
+        if (ok) {
+          const size_t o = (size_t)(o0 + (uint32_t)(b * a.L));
+          S* p = static_cast<S*>(a.out) + o;
+          if (a.nt) st1<true>(p, ac);
+          else st1<false>(p, ac);
+          if constexpr (R::kGrad) {
+            S* g = static_cast<S*>(a.out2) + 2 * o;
+            if (a.nt) st2<true>(g, ax, ay);
+            else st2<false>(g, ax, ay);
+          }
+        }
+      }
+    }
+  }
+}
+
 // Up to 16 waves per workgroup (at most 128 registers per lane), 8 for the
 // three-slice FP64 Laplacian and the FP64 one-pass pairs of more than one
 // slice per step, which need more registers.
@@ -1551,6 +1662,9 @@ __device__ __forceinline__ void tile_work(const TileArgs& a, int64_t tile, int c
       // the few nodes outside the blocks: one slice at a time, which keeps
       // them from setting the kernel's register count
       for (int32_t tn = n0 + q; tn < nnodes; tn += W) tile_eval<S, OP, 1>(a, lds, tn, data_off, colB, k0, kmain, lane);
+    } else {
+      n0 = nblk * NB;
+      tile_short<S, OP, NB>(a, lds, nblk, data_off, colB, k0, rem, tj, tt, wave, W);
     }
     if (pack) tile_tail<S, OP>(a, lds, nnodes, data_off, colB, k0, kmain, rem, tj, tt, n0, q, W, lane);
   } else {
@@ -2704,12 +2818,33 @@ hipError_t launch_op(int op, int dtype, const DevTables& t, const NodeOrder& ord
 
 namespace {
 
-Shape resolve_path(int op, int dtype, int nlev, const Shape& sh) {
+Shape resolve_path(int op, int dtype, int nlev, int64_t V, const Shape& sh) {
   Shape e = sh;
   if (e.lds_tiles != 0) return e;
   if (nlev <= 32) {
-    e.lds_tiles = 2;
-    return e;
+    // Columns of at most 32 levels: the gather gives a wave 64 / nlev nodes
+    // and reads each neighbour's column from L2, in pieces of less than a
+    // cache line; the tiles read every column once, in whole tiles.  19
+    // levels, gather -> tiles: O640 FP32 gradient 253 -> 102 us, divergence
+    // 303 -> 118, Laplacian 443 -> 124, divergence and curl 603 -> 160; FP64
+    // divergence 426 -> 198, BF16 Laplacian 373 -> 96; 32 levels FP32
+    // Laplacian 639 -> 153.  Below eight levels the tables, not the columns,
+    // are most of the traffic, and a tile's are larger (O640 x 2 FP32
+    // divergence 33 -> 40 us, O320 x 4 FP64 Laplacian 30 -> 36); at eight the
+    // two are level for the slowest operators (O320 BF16 divergence 17.8 ->
+    // 17.6) and the others gain (FP32 Laplacian 34 -> 27).  In small fields a tile's
+    // start (tables, then data, then arithmetic: 5-10 us) shows: BF16
+    // divergence at 10 levels 7.3 -> 10.2 us at O160, 10.2 -> 11.2 at O200
+    // (1.7 million values), 23.3 -> 19.3 at O320 (4.2 million).  A shape that sets a parameter of
+    // the gather's keeps it.
+    const Shape def;
+    if (nlev < kShortTileLevels || V * nlev < kShortTileValues || e.row_window || e.lanes_per_node ||
+        e.band_rows || e.run_nodes || e.slices_per_iter || e.nodes_per_wave != def.nodes_per_wave ||
+        e.waves_per_block != def.waves_per_block) {
+      e.lds_tiles = 2;
+      return e;
+    }
+    e.short_tiles = true;
   }
   // Measured defaults at O1280 x 137 (rows: mode, KiB, tile rows, computing
   // and copying waves of the persistent form): scalar-input 1-ring operators,
@@ -2777,8 +2912,8 @@ Shape resolve_path(int op, int dtype, int nlev, const Shape& sh) {
 // do most BF16 columns, half as wide (gradient 330 -> 344 us, divergence and
 // curl 368 -> 382 at 91 levels): they keep the plain order.
 // The other paths, without a tile's reuse of its own halo, keep the eighths.
-Shape resolve_shape(int op, int dtype, int nlev, const Shape& sh) {
-  Shape e = resolve_path(op, dtype, nlev, sh);
+Shape resolve_shape(int op, int dtype, int nlev, int64_t V, const Shape& sh) {
+  Shape e = resolve_path(op, dtype, nlev, V, sh);
   if (e.xcd_remap >= 0) return e;
   const int k = kernel_op(op);
   if (!(e.lds_tiles == 3 && uses_tiles(op, dtype, nlev, e))) e.xcd_remap = 1;
@@ -2788,7 +2923,7 @@ Shape resolve_shape(int op, int dtype, int nlev, const Shape& sh) {
 
 bool uses_tiles(int op, int dtype, int nlev, const Shape& sh) {
   (void)op;
-  if (nlev <= 32) return false;
+  if (nlev <= 32 && !sh.short_tiles) return false;
   if (dtype == DT_BF16) return sh.lds_tiles == 3;   // BF16: one-tile form only
   return (dtype == DT_F32 || dtype == DT_F64) && (sh.lds_tiles == 1 || sh.lds_tiles == 3);
 }

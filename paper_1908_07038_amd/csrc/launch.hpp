@@ -52,17 +52,20 @@ struct Shape {
   int row_window = 0;        // 0: default (on), 1: on, 2: off -- row-window walk of 1-ring operators
   int lds_tiles = 0;         // 0: default (per operator and dtype, see resolve_shape), 1: on
                              // (persistent, double buffered), 2: off, 3: on (one tile per
-                             // workgroup) -- LDS tile path (FP32/FP64, > 32 levels)
+                             // workgroup) -- LDS tile path (> 32 levels)
   int tile_kb = 0;           // 0: kDefaultTileKB; LDS budget of one tile in KiB (8..64)
   int tile_waves = 0;        // 0: 6; consumer waves per persistent tile workgroup
   int producer_waves = 0;    // 0: 2; producer (copy) waves per persistent tile workgroup
   int tile_wgs_per_cu = 0;   // 0: 1; persistent tile workgroups per CU
   int tile_levels = 0;       // 0: automatic; else levels per column chunk of a tile
+  bool short_tiles = false;  // set by resolve_shape: columns of at most 32 levels on LDS tiles
   int batch_mode = 0;        // batched plans: 0 default (persistent), 1 persistent tiled, 2 field launches
   int batch_claim = 0;       // batched persistent form: tiles per work claim (0: kDefaultBatchClaim)
 };
 
 constexpr int kXcdSchedule = 2;
+constexpr int kShortTileLevels = 8;             // fewest levels and values (nodes x levels) of a field of
+constexpr int64_t kShortTileValues = 5 << 19;   // columns of at most 32 levels that takes LDS tiles
 constexpr int kDefaultBandRows = 32;
 constexpr int kDefaultRunNodes = 16;
 constexpr int kDefaultWindowRunNodes = 64;
@@ -115,7 +118,7 @@ struct TileGeom {
 };
 // The shape a launch runs with: lds_tiles = 0 picks the path (and tile
 // parameters left at 0) from per-operator, per-dtype defaults.
-Shape resolve_shape(int op, int dtype, int nlev, const Shape& sh);
+Shape resolve_shape(int op, int dtype, int nlev, int64_t V, const Shape& sh);
 bool uses_tiles(int op, int dtype, int nlev, const Shape& sh);
 // Name of the kernel template instance a single-field launch with the
 // resolved shape runs, e.g. "k_tile<float, 0, 3>".
