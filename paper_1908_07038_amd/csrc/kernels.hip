@@ -2191,6 +2191,14 @@ hipError_t launch_remap_t(const int32_t* nodes, const void* w, int64_t V, int64_
 // With STG (whole columns in one block) the wave's G consecutive output
 // columns are staged in LDS and written as one contiguous run in units of
 // `unit` bytes: measured 15-20 % faster than the groups' own 64-byte pieces.
+// Workgroups alternate between the two ends of the nodes and meet at the
+// equator: where the target's rows keep all their longitudes, polar nodes
+// have up to ~190 entries, a serial chain of loads, which starts first and
+// ends while the many nodes of one or two entries stream; and the nodes in
+// flight lie along two pairs of rows, few DRAM pages.  O640 <- F320 x 91
+// FP64: an eighth of the nodes per XCD 625 us, plain order 466, from both
+// ends 415 (the arrays once at 6.4 TB/s: 287); O1280 <- F640 x 137 FP32 1658,
+// 1225, 1202 us, FP64 3.47, 2.60, 2.40 ms.
 typedef double f64x2_e __attribute__((ext_vector_type(2), aligned(8)));   // two levels, element-aligned
 template <class S, int VEC>
 struct VecOf {
@@ -2206,7 +2214,7 @@ __global__ __launch_bounds__(256) void k_remap_adj(const int64_t* __restrict__ o
                                                    const void* __restrict__ wv, const int32_t* __restrict__ ht,
                                                    const void* __restrict__ hwv, const S* __restrict__ in,
                                                    S* __restrict__ out, int64_t V, int L, int lanes, int64_t nblocks,
-                                                   int remap, int unit) {
+                                                   int unit) {
   using C = typename Traits<S>::C;
   using C2 = typename Traits<S>::C2;
   using VT = typename VecOf<S, VEC>::T;
@@ -2214,8 +2222,8 @@ __global__ __launch_bounds__(256) void k_remap_adj(const int64_t* __restrict__ o
   extern __shared__ __align__(16) char smem[];
   const C* __restrict__ w = static_cast<const C*>(wv);
   const C* __restrict__ hw = static_cast<const C*>(hwv);
-  const int64_t lb = logical_block(blockIdx.x, nblocks, remap);
-  if (lb >= nblocks) return;
+  const int64_t b = blockIdx.x;
+  const int64_t lb = b & 1 ? nblocks - 1 - (b >> 1) : b >> 1;
   const int W = blockDim.x >> 6;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int G = 64 / lanes;
@@ -2360,7 +2368,6 @@ hipError_t launch_remap_adj_ns(const int64_t* off, const int32_t* tt, const void
   constexpr int W = 4;
   const int64_t groups = (V + G - 1) / G;
   const int64_t nblocks = (groups + W - 1) / W;
-  const int64_t grid = (nblocks + 7) / 8 * 8;
   const bool o32 = (uint64_t)P * (uint64_t)nlev * sizeof(S) < (1ull << 32);
   const size_t lds = (size_t)W * G * nlev * sizeof(S);
   const bool stage = nlev <= lanes * VEC * NS && lds <= 32768;
@@ -2372,17 +2379,17 @@ hipError_t launch_remap_adj_ns(const int64_t* off, const int32_t* tt, const void
       unit = u;
       break;
     }
-  const dim3 g((unsigned)grid), b(64 * W);
+  const dim3 g((unsigned)nblocks), b(64 * W);
   // 16 lanes with exactly the slices the column needs: constant slice
   // offsets (4- and 2-byte data; measured 3 % and 8 % faster at O1280 x 137
   // <- F640, but 6 % slower for the FP64 16-byte loads)
   const bool exact = VEC == 1 && lanes == 16 && (nlev + 15) / 16 == NS;
 #define RADJ_LAUNCH(O, T)                                                                                             \
   hipLaunchKernelGGL((k_remap_adj<S, NS, VEC, O, T>), g, b, T ? lds : 0, st, off, tt, w, ht, hw, src, dst, V, nlev, \
-                     lanes, nblocks, 1, unit)
+                     lanes, nblocks, unit)
   if (o32 && stage && exact) {
     hipLaunchKernelGGL((k_remap_adj<S, NS, VEC, true, true, true>), g, b, lds, st, off, tt, w, ht, hw, src, dst, V,
-                       nlev, lanes, nblocks, 1, unit);
+                       nlev, lanes, nblocks, unit);
   } else if (o32) {
     if (stage) RADJ_LAUNCH(true, true);
     else RADJ_LAUNCH(true, false);
