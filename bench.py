@@ -50,7 +50,7 @@ OP_ELEMS = {"gradient": (1, 2), "divergence": (2, 1), "laplacian": (1, 1), "grad
             "divergence_gradient_adjoint": (2, 2)}
 OP_SWEEPS = {"gradient": 1, "divergence": 1, "laplacian": 2, "gradient_laplacian": 3, "gradient_adjoint": 1,
              "divergence_adjoint": 1, "conservation": 0, "divergence_gradient_adjoint": 2}
-CONSERVATION_KERNELS = "k_cons_partial + k_cons_final"
+CONSERVATION_KERNELS = "k_cons_flat (FP64: k_cons_partial) + k_cons_final"
 
 
 def kernel_names(pa, mesh, dtype_code, L):
@@ -619,7 +619,7 @@ def summarize_profiles(stats_db, fetch_db, write_db, stats_cmd, pmc_cmd):
             if n not in per["write"]:
                 continue
             lines.append(f"{src} {op} {dname} {per['fetch'][n] * 1024 * cal_f:.0f} {per['write'][n] * 1024 * cal_w:.0f}")
-        cons = [n for n in per["fetch"] if n.startswith(f"k_cons_partial<{ty},")]
+        cons = [n for n in per["fetch"] if n.startswith((f"k_cons_flat<{ty},", f"k_cons_partial<{ty},"))]
         if cons:
             f_ = sum(per["fetch"][n] for n in cons[:1]) * 1024 * cal_f
             w_ = sum(per["write"].get(n, 0.0) for n in cons[:1]) * 1024 * cal_w

@@ -2516,6 +2516,116 @@ __global__ __launch_bounds__(64 * kConsWaves) void k_cons_partial(const S* __res
   }
 }
 
+// Columns of at most kConsFlatLevels levels: the field as one run of numbers.
+// A workgroup's step covers kConsUnroll groups of g consecutive nodes; thread
+// t owns numbers t * VEC ... of every group (16 bytes; FP64 32), and as g * L
+// is a multiple of VEC these keep their levels and their node of the group
+// from step to step, whatever the column's length.  So every lane has work
+// (94 % at 137 levels, where 64-level slices fill 71 % of theirs, and 19
+// levels 30 %), every load is 16 bytes, and the groups in flight on the GPU
+// are one run of memory.  At the end the g sums of a level are combined in
+// node order, in two stages.  ALN: the field is 16-byte aligned; else the
+// same numbers are loaded one at a time.  Bound by memory reads; one
+// workgroup of 16 waves per CU, which keeps the partial sums few (1024
+// workgroups: O640 x 19 FP32 42 us, 256: 30).  Slices of 64 levels -> this:
+// O1280 x 137 FP32 694 -> 661 us (5.5 TB/s), BF16 617 -> 335, O640 x 91 FP32
+// 152 -> 114, x 19 113 -> 30, x 2 106 -> 21, O320 x 60 FP64 44 -> 39.
+constexpr int kConsFlatLevels = 1024;
+constexpr int kConsFlatThreads = 1024;
+constexpr int kConsFlatParts = 256;   // most workgroups: one per CU
+
+template <class S>
+constexpr int kConsVec = sizeof(S) == 8 ? 4 : 16 / (int)sizeof(S);
+template <class S>
+constexpr int kConsUnroll = sizeof(S) == 4 ? 4 : 2;
+
+template <class S, bool ALN>
+__global__ __launch_bounds__(kConsFlatThreads) void k_cons_flat(const S* __restrict__ div, const double* __restrict__ vol,
+                                                                int64_t V, int L, int g, double* __restrict__ part) {
+  constexpr int VEC = kConsVec<S>, U = kConsUnroll<S>;
+  struct alignas(16) Pack {
+    S x[VEC];
+  };
+  __shared__ double red[kConsFlatThreads * VEC];
+  const int t = threadIdx.x;
+  const int per = g * L / VEC;   // vectors of a group
+  double s[VEC], ab[VEC];
+#pragma unroll
+  for (int c = 0; c < VEC; ++c) s[c] = ab[c] = 0.0;
+  if (t < per) {
+    // the group's nodes of the first and the last number, and how many numbers
+    // belong to the first; columns shorter than a vector may span more
+    const int na = t * VEC / L, nb = (t * VEC + VEC - 1) / L, m = (na + 1) * L - t * VEC;
+    const bool two = L >= VEC;
+    const int64_t step = (int64_t)gridDim.x * U * g;
+    auto load = [&](int64_t n0, Pack& x, double& va, double& vb) {
+      const S* p = div + n0 * (int64_t)L + t * VEC;
+      if constexpr (ALN) {
+        x = *reinterpret_cast<const Pack*>(p);
+      } else {
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) x.x[c] = p[c];
+      }
+      va = vol[n0 + na];
+      vb = vol[n0 + nb];
+    };
+    auto add = [&](int64_t n0, const Pack& x, double va, double vb) {
+#pragma unroll
+      for (int c = 0; c < VEC; ++c) {
+        double w = c < m ? va : vb;
+        if (!two) w = vol[n0 + (t * VEC + c) / L];
+        const double q = w * (double)ld1(&x.x[c]);
+        s[c] += q;
+        ab[c] += fabs(q);
+      }
+    };
+    int64_t n = (int64_t)blockIdx.x * U * g;
+    for (; n + U * g <= V; n += step) {
+      Pack x[U];
+      double va[U], vb[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) load(n + u * g, x[u], va[u], vb[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u) add(n + u * g, x[u], va[u], vb[u]);
+    }
+    // the last groups: the mesh ends at a multiple of VEC numbers, so a vector
+    // whose last number is there is there
+    for (int u = 0; u < U; ++u, n += g)
+      if (n + nb < V) {
+        Pack x;
+        double va, vb;
+        load(n, x, va, vb);
+        add(n, x, va, vb);
+      }
+  }
+  // red[j * L + k]: level k's sum over node j of the groups.  Thread (r, k)
+  // adds nodes r, r + R, ..., thread k the R sums.
+  int R = (int)blockDim.x / L;
+  R = R < 32 ? R : 32;
+  if (R > g) R = g;
+  const int r = t / L, k = t - r * L;
+#pragma unroll
+  for (int which = 0; which < 2; ++which) {
+    __syncthreads();
+    if (t < per) {
+#pragma unroll
+      for (int c = 0; c < VEC; ++c) red[t * VEC + c] = which ? ab[c] : s[c];
+    }
+    __syncthreads();
+    double a = 0.0;
+    if (r < R)
+      for (int j = r; j < g; j += R) a += red[j * L + k];
+    __syncthreads();
+    if (r < R) red[t] = a;
+    __syncthreads();
+    if (t < L) {
+      a = red[t];
+      for (int j = 1; j < R; ++j) a += red[j * L + t];
+      part[((int64_t)blockIdx.x * L + t) * 2 + which] = a;
+    }
+  }
+}
+
 // One workgroup per level: thread t sums partials t, t + 256, ... in order,
 // then a fixed binary tree combines the 256 thread sums.
 __global__ __launch_bounds__(256) void k_cons_final(const double* __restrict__ part, int nparts, int L,
@@ -3187,7 +3297,43 @@ int conservation_parts(int64_t V, int nlev) {
 
 hipError_t launch_conservation(int dtype, const double* vol, int64_t V, int nlev, const void* div, double* scratch,
                                double* out_sum, double* out_abs, hipStream_t stream) {
-  const int parts = conservation_parts(V, nlev);
+  int parts = conservation_parts(V, nlev);
+  const int64_t es = dtype == DT_F64 ? 8 : dtype == DT_F32 ? 4 : 2;
+  const int64_t vec = es == 2 ? 8 : 4;
+  // the flat form, but for FP64 fields of over 2 GiB, where the slices are
+  // ahead (O1280 x 137: 1.23 ms against 1.30; O640 x 137, 1.8 GB: 334 us
+  // against 328)
+  const bool large64 = es == 8 && V * nlev > (int64_t)1 << 28;
+  if (nlev <= kConsFlatLevels && V % vec == 0 && !large64) {
+    if (parts > kConsFlatParts) parts = kConsFlatParts;
+    // nodes of a group: as many as the threads hold, no more than a
+    // workgroup's part, in steps that keep whole vectors
+    int64_t q = vec;
+    while (q > 1 && (q / 2) * nlev % vec == 0) q /= 2;
+    const int64_t most = kConsFlatThreads * vec / nlev / q * q, part = ((V + parts - 1) / parts + q - 1) / q * q;
+    const int64_t gn = most < part ? most : part;
+    const int64_t thr = (gn * nlev / vec + 63) / 64 * 64;
+    const int threads = (int)(thr > (nlev + 63) / 64 * 64 ? thr : (nlev + 63) / 64 * 64);
+    const bool aln = ((uintptr_t)div & 15u) == 0;
+#define ATLAS_CONS(DT, S)                                                                                           \
+  case DT:                                                                                                          \
+    if (aln)                                                                                                        \
+      hipLaunchKernelGGL((k_cons_flat<S, true>), dim3(parts), dim3(threads), 0, stream, static_cast<const S*>(div), \
+                         vol, V, nlev, (int)gn, scratch);                                                           \
+    else                                                                                                            \
+      hipLaunchKernelGGL((k_cons_flat<S, false>), dim3(parts), dim3(threads), 0, stream,                            \
+                         static_cast<const S*>(div), vol, V, nlev, (int)gn, scratch);                               \
+    break;
+    switch (dtype) {
+      ATLAS_CONS(DT_F64, double) ATLAS_CONS(DT_F32, float) ATLAS_CONS(DT_BF16, bf16_t)
+#undef ATLAS_CONS
+      default: return hipErrorInvalidValue;
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_cons_final, dim3(nlev), dim3(256), 0, stream, scratch, parts, nlev, out_sum, out_abs);
+    return hipGetLastError();
+  }
   const int64_t chunk = (V + parts - 1) / parts;
   const dim3 g(parts), b(64 * kConsWaves);
   // slices of the column's last 256-level block
