@@ -372,7 +372,7 @@ typedef struct {
                                columns when 48 (1-ring) or 96 (two-ring)
                                columns fit the budget, else equal chunks);
                                ignored if one node's stencil would not fit    */
-  int32_t batch_mode;       /* batched plans: 1 (the default) one persistent
+  int32_t batch_mode;       /* batched plans: 1 one persistent
                                launch per operator over all tracers, on the
                                LDS tiles of the one-tile form (tile_kb,
                                band_rows, run_nodes, tile_levels and
@@ -380,7 +380,11 @@ typedef struct {
                                its workgroups per CU; an operator whose tiles
                                do not fit runs as field launches); 2 the
                                single-field launch of each (operator, tracer)
-                               with the mesh's shapes, operators outermost    */
+                               with the mesh's shapes, operators outermost;
+                               0 persistent, but for a shape of defaults only
+                               on at least 5 x 2^22 nodes x levels a tracer of
+                               at most 8 different level counts: field
+                               launches on the default shapes                 */
   int32_t batch_claim;      /* batched persistent form: consecutive tiles a
                                workgroup takes per claim on its XCD's work
                                counter, 1..64 (0: 4)                          */
@@ -405,15 +409,15 @@ int atlas_batch_create(atlas_mesh_t mesh, int dtype, const atlas_tracer_desc_t* 
 /* Enqueue the plan's work on `stream`, operators in the order of the bits
  * above: in the persistent form one launch per operator (as many workgroups
  * as the CUs hold at once, each walking its XCD's share of the (tracer,
- * tile, chunk) items); with batch_mode 2 the single-field launch of every
+ * tile, chunk) items); in the field form the single-field launch of every
  * tracer for each operator.  A plan whose divergence and gradient adjoint
  * take the same input field in every tracer, with no output of either
- * overlapping an input, runs those two as one persistent launch on the
- * divergence's shape (as atlas_nabla_divergence_gradient_adjoint: the same
- * values; in FP64 only on shapes of at most 8 waves, else as two launches);
- * atlas_batch_tune still times them one at a time.  The
- * persistent form
- * allocates nothing and never synchronises; the field form does so only the
+ * overlapping an input or an output of the other, runs those two as one, in
+ * the divergence's form and shape (as atlas_nabla_divergence_gradient_adjoint:
+ * the same values; persistent in FP64 only on shapes of at most 8 waves, else
+ * as two launches); atlas_batch_tune still times them one at a time.  The
+ * persistent form and the field form on default shapes
+ * allocate nothing and never synchronise; with batch_mode 2 a plan does so only the
  * first time a (operator, dtype, level count) is used on the mesh, when it
  * builds node orders, tilings and records -- after one eager run it too may be
  * recorded into a HIP graph by stream capture. */

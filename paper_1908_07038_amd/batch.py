@@ -1,11 +1,12 @@
 """Batched multi-tracer plans over many fields with different level counts.
 
-By default each operator is one persistent launch over every tracer: the
+By default each operator of a plan of small fields is one persistent launch
+over every tracer, of large ones each tracer's own launch.  Persistent: the
 workgroups of each XCD walk that XCD's share of the (tracer, tile, level
 chunk) items on the LDS tiles of the single-field one-tile form, with the
 same arithmetic per output element, so results equal the single-field calls
-bit for bit.  ``tune={"batch_mode": 2}`` runs the tracers' single-field
-launches instead.  Either form can be replayed as a HIP graph."""
+bit for bit.  ``tune={"batch_mode": 1}`` asks for the persistent form,
+``{"batch_mode": 2}`` for the tracers' single-field launches.  Either form can be replayed as a HIP graph."""
 
 import ctypes
 

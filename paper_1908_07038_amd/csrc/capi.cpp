@@ -12,6 +12,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <set>
 #include <stdexcept>
 #include <string>
 #include <vector>
@@ -370,8 +371,10 @@ int call_tiles(atlas_mesh_t mesh, int op, int dtype, TileGeom& tg, const Shape& 
   return ATLAS_OK;
 }
 
+// build: only build what the call needs on first use (tiles, records, node
+// order); nothing is launched.
 int run_op(atlas_mesh_t mesh, int op, int dtype, int32_t nlev, const void* in, void* out, void* stream,
-           const Shape* shape_override = nullptr) {
+           const Shape* shape_override = nullptr, bool build = false) {
   int rc = check_mesh_device(mesh);
   if (rc) return rc;
   const size_t es = dtype_size(dtype);
@@ -398,6 +401,7 @@ int run_op(atlas_mesh_t mesh, int op, int dtype, int32_t nlev, const void* in, v
   // tiles asked for and a tile geometry fits the budget
   if (tg.KL > 0 && (rc = call_tiles(mesh, op, dtype, tg, sh, dt, rec, (hipStream_t)stream))) return rc;
   if (tg.KL > 0) {
+    if (build) return ATLAS_OK;
     hipError_t e = launch_tiles(op, dtype, dt, rec, nlev, in, out, sh, mesh->num_cus, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, kOpName[op]);
     return ATLAS_OK;
@@ -419,6 +423,7 @@ int run_op(atlas_mesh_t mesh, int op, int dtype, int32_t nlev, const void* in, v
   } catch (const std::exception& ex) {
     return fail(ATLAS_EHIP, ex.what());
   }
+  if (build) return ATLAS_OK;
   hipError_t e = launch_op(op, dtype, mesh->tables(dtype), order, V, nlev, in, out, sh, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, kOpName[op]);
   return ATLAS_OK;
@@ -629,9 +634,11 @@ namespace {
 // The divergence and a second divergence-form operator (op2: OP_CURL or
 // OP_GRADT) of one vector field: one pass of the dual kernel (fused op
 // OP_DIVCURL or OP_DIVGRADT) on the divergence's launch shape when that is
-// the one-tile LDS form, else the two operators one after the other.
+// the one-tile LDS form, else the two operators one after the other (build:
+// as run_op's).
 int divergence_pair(atlas_mesh_t mesh, int fused, int op2, const char* name, int dtype, int32_t nlev,
-                    const void* uv, void* div, void* out2, void* stream) {
+                    const void* uv, void* div, void* out2, void* stream, const Shape* shape_override = nullptr,
+                    bool build = false) {
   int rc = check_mesh_device(mesh);
   if (rc) return rc;
   const size_t es = dtype_size(dtype);
@@ -648,7 +655,8 @@ int divergence_pair(atlas_mesh_t mesh, int fused, int op2, const char* name, int
                                   " must not overlap");
   DeviceGuard g(mesh->device);
   if (!g.ok) return fail(ATLAS_EHIP, "cannot select the mesh's device");
-  const Shape sh = resolve_shape(fused, dtype, nlev, V, mesh->shape[OP_DIV][dtype]);
+  const Shape sh =
+      resolve_shape(fused, dtype, nlev, V, shape_override ? *shape_override : mesh->shape[OP_DIV][dtype]);
   TileGeom tg;
   if (sh.lds_tiles == 3 && uses_tiles(fused, dtype, nlev, sh)) tg = tile_geom(fused, dtype, nlev, sh);
   if (dtype == ATLAS_BF16 && ((uintptr_t)uv & 3u)) tg.KL = 0;
@@ -656,12 +664,13 @@ int divergence_pair(atlas_mesh_t mesh, int fused, int op2, const char* name, int
   const void* rec = nullptr;
   if (tg.KL > 0 && (rc = call_tiles(mesh, fused, dtype, tg, sh, dt, rec, (hipStream_t)stream))) return rc;
   if (tg.KL > 0) {
+    if (build) return ATLAS_OK;
     hipError_t e = launch_tiles(fused, dtype, dt, rec, nlev, uv, div, sh, mesh->num_cus, (hipStream_t)stream, out2);
     if (e != hipSuccess) return hip_fail(e, name);
     return ATLAS_OK;
   }
-  if ((rc = run_op(mesh, OP_DIV, dtype, nlev, uv, div, stream))) return rc;
-  return run_op(mesh, op2, dtype, nlev, uv, out2, stream);
+  if ((rc = run_op(mesh, OP_DIV, dtype, nlev, uv, div, stream, shape_override, build))) return rc;
+  return run_op(mesh, op2, dtype, nlev, uv, out2, stream, shape_override, build);
 }
 
 }  // namespace
@@ -1118,6 +1127,8 @@ struct atlas_batch_s {
   std::vector<atlas_tracer_desc_t> descs;
   BatchOp ops[4];
   BatchOp pair;             // divergence and gradient adjoint in one launch (see plan_pairs)
+  bool fields = false;      // the library's choice of field launches (see plan_fields)
+  bool pairs = false;       // plan_pairs: the divergence and gradient adjoint may run as one
   hipStream_t capture_stream = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -1151,6 +1162,36 @@ namespace {
 
 // Persistent form (batch_mode 0 or 1) unless field launches are asked for.
 bool plan_persistent(const Shape& sh) { return sh.batch_mode != 2; }
+
+// Whether a plan left at the library's defaults runs the tracers' field
+// launches: where a launch fills the GPU many times over, each field's own
+// kernel, at its own workgroup size, LDS and slice count, beats one persistent
+// kernel compiled and sized for the largest of them.  Gradient, divergence
+// with gradient adjoint and divergence adjoint, persistent against field
+// launches: O320, 16 tracers of 1-137 levels FP32 5.45 against 4.56 ms, FP64
+// 9.62 against 9.08, of 33 and 48 levels 3.42 against 3.07 and (17 million
+// values a tracer) 5.95 against 6.09; O160, of 1-137 (8 million) FP32 1.51
+// against 1.50, FP64 2.58 against 2.82; O64 385 against 468 us.  Each level
+// count has tilings and records of its own, which bounds the different ones.
+bool plan_fields(const atlas_batch_s* b) {
+  int64_t levels = 0;
+  std::set<int32_t> counts;
+  for (const atlas_tracer_desc_t& d : b->descs) {
+    levels += d.nlev;
+    counts.insert(d.nlev);
+  }
+  if (b->mesh->host.V * levels < kBatchFieldValues * (int64_t)b->descs.size() ||
+      counts.size() > (size_t)kBatchFieldCounts)
+    return false;
+  atlas_tune_t def{};
+  shape_out(Shape(), &def);
+  for (int o = 0; o < 4; ++o) {
+    atlas_tune_t t{};
+    shape_out(b->shape[o], &t);
+    if (memcmp(&t, &def, sizeof t)) return false;
+  }
+  return true;
+}
 
 // Level count whose tiling a tracer of L levels uses: L rounded up to a
 // power of two, at most the plan's largest L.  Tracers of similar depth share
@@ -1257,9 +1298,9 @@ int plan_op(atlas_batch_s* b, int o, BatchOp& bo, bool pair = false) {
 
 // Whether the plan's divergence and gradient adjoint can run as one pass:
 // both asked for, on the same input field in every tracer, and no output of
-// either overlapping an input of any tracer (run one after the other, the
-// divergence of every tracer precedes every gradient adjoint; in one pass
-// they interleave).
+// either overlapping an input of any tracer or an output of the other (run
+// one after the other, the divergence of every tracer precedes every gradient
+// adjoint; in one pass they interleave).
 bool plan_pairs(const atlas_batch_s* b) {
   if ((b->mask & ((1u << OP_DIV) | (1u << OP_GRADT))) != ((1u << OP_DIV) | (1u << OP_GRADT))) return false;
   const size_t es = dtype_size(b->dtype);
@@ -1269,15 +1310,43 @@ bool plan_pairs(const atlas_batch_s* b) {
   for (const atlas_tracer_desc_t& d : b->descs)
     for (const atlas_tracer_desc_t& e : b->descs) {
       const size_t nd = (size_t)V * d.nlev * es, ne = (size_t)V * e.nlev * es;
-      if (overlaps(d.out[OP_DIV], nd, e.in[OP_DIV], 2 * ne) || overlaps(d.out[OP_GRADT], nd, e.in[OP_DIV], 2 * ne))
+      if (overlaps(d.out[OP_DIV], nd, e.in[OP_DIV], 2 * ne) || overlaps(d.out[OP_GRADT], nd, e.in[OP_DIV], 2 * ne) ||
+          overlaps(d.out[OP_DIV], nd, e.out[OP_GRADT], ne))
         return false;
     }
   return true;
 }
 
-// (Re)build the device work tables of a plan for its operators' shapes.
+// One operator over every tracer in field launches, on the mesh's shapes or,
+// where the field form is the library's choice, the default ones; pair: the
+// divergence with the gradient adjoint; build: see run_op.
+int plan_run_fields(atlas_batch_s* b, int o, bool pair, hipStream_t st, bool build = false) {
+  const Shape def;
+  const Shape* sh = b->fields ? &def : nullptr;
+  for (const atlas_tracer_desc_t& d : b->descs) {
+    int rc = pair ? divergence_pair(b->mesh, OP_DIVGRADT, OP_GRADT, "divergence_gradient_adjoint", b->dtype, d.nlev,
+                                    d.in[OP_DIV], d.out[OP_DIV], d.out[OP_GRADT], st, sh, build)
+                  : run_op(b->mesh, o, b->dtype, d.nlev, d.in[o], d.out[o], st, sh, build);
+    if (rc) return rc;
+  }
+  return ATLAS_OK;
+}
+
+// (Re)build what a plan needs for its operators' shapes: the device work
+// tables of the persistent form, or what the field launches of the library's
+// choice use.
 int plan_upload(atlas_batch_s* b) {
   b->release_tables();
+  b->pairs = plan_pairs(b);
+  b->fields = plan_fields(b);
+  if (b->fields) {
+    for (int o = 0; o < 4; ++o) {
+      if (!(b->mask & (1u << o)) || (b->pairs && o == OP_GRADT)) continue;
+      int rc = plan_run_fields(b, o, b->pairs && o == OP_DIV, nullptr, true);
+      if (rc) return rc;
+    }
+    return ATLAS_OK;
+  }
   for (int o = 0; o < 4; ++o) {
     if (!(b->mask & (1u << o)) || !plan_persistent(b->shape[o])) continue;
     int rc = plan_op(b, o, b->ops[o]);
@@ -1285,7 +1354,7 @@ int plan_upload(atlas_batch_s* b) {
   }
   // the divergence and the gradient adjoint of the same fields in one
   // persistent launch, on the divergence's shape, where it fits
-  if (plan_persistent(b->shape[OP_DIV]) && plan_pairs(b)) {
+  if (plan_persistent(b->shape[OP_DIV]) && b->pairs) {
     int rc = plan_op(b, OP_DIV, b->pair, true);
     if (rc) return rc;
   }
@@ -1296,39 +1365,38 @@ int plan_upload(atlas_batch_s* b) {
 // single-field launches in order.
 int plan_run_op(atlas_batch_s* b, int o, hipStream_t st) {
   const BatchOp& bo = b->ops[o];
-  if (bo.tiled) {
-    hipError_t e = launch_tiles_batched(o, b->dtype, bo.tr, bo.pre, (int)b->descs.size(), bo.ctr, bo.claim, bo.lds,
-                                        bo.waves, bo.grid, bo.umax, st);
-    return e != hipSuccess ? hip_fail(e, kOpName[o]) : ATLAS_OK;
-  }
-  for (const atlas_tracer_desc_t& d : b->descs) {
-    int rc = run_op(b->mesh, o, b->dtype, d.nlev, d.in[o], d.out[o], st);
-    if (rc) return rc;
-  }
-  return ATLAS_OK;
+  if (!bo.tiled) return plan_run_fields(b, o, false, st);
+  hipError_t e = launch_tiles_batched(o, b->dtype, bo.tr, bo.pre, (int)b->descs.size(), bo.ctr, bo.claim, bo.lds,
+                                      bo.waves, bo.grid, bo.umax, st);
+  return e != hipSuccess ? hip_fail(e, kOpName[o]) : ATLAS_OK;
 }
 
 // Operators outermost, in the order of their bits; the divergence and
-// gradient adjoint pair, where planned, in the divergence's place.
+// gradient adjoint pair, where possible, in the divergence's place and form.
 int plan_run(atlas_batch_s* b, hipStream_t st) {
+  const bool field_pair = b->pairs && (b->fields || !plan_persistent(b->shape[OP_DIV]));
   for (int o = 0; o < 4; ++o) {
     if (!(b->mask & (1u << o))) continue;
-    if (b->pair.tiled && (o == OP_DIV || o == OP_GRADT)) {
-      if (o == OP_GRADT) continue;
+    int rc;
+    if ((b->pair.tiled || field_pair) && o == OP_GRADT) continue;
+    if (b->pair.tiled && o == OP_DIV) {
       const BatchOp& bo = b->pair;
       hipError_t e = launch_tiles_batched(OP_DIVGRADT, b->dtype, bo.tr, bo.pre, (int)b->descs.size(), bo.ctr, bo.claim,
                                           bo.lds, bo.waves, bo.grid, bo.umax, st);
-      if (e != hipSuccess) return hip_fail(e, "divergence_gradient_adjoint");
-      continue;
+      rc = e != hipSuccess ? hip_fail(e, "divergence_gradient_adjoint") : ATLAS_OK;
+    } else if (field_pair && o == OP_DIV) {
+      rc = plan_run_fields(b, o, true, st);
+    } else {
+      rc = plan_run_op(b, o, st);
     }
-    int rc = plan_run_op(b, o, st);
     if (rc) return rc;
   }
   return ATLAS_OK;
 }
 
-// Whether every operator of the plan runs as one persistent launch.
-bool plan_all_tiled(const atlas_batch_s* b) {
+// Whether a run of the plan has nothing left to build.
+bool plan_ready(const atlas_batch_s* b) {
+  if (b->fields) return true;
   for (int o = 0; o < 4; ++o)
     if ((b->mask & (1u << o)) && !b->ops[o].tiled && !(b->pair.tiled && (o == OP_DIV || o == OP_GRADT)))
       return false;
@@ -1404,7 +1472,7 @@ int atlas_batch_graph_launch(atlas_batch_t plan, void* stream) {
       e = hipStreamCreateWithFlags(&plan->capture_stream, hipStreamNonBlocking);
       if (e != hipSuccess) return hip_fail(e, "hipStreamCreateWithFlags");
     }
-    if (!plan_all_tiled(plan)) {
+    if (!plan_ready(plan)) {
       // one eager pass, in order on the caller's stream, builds every node
       // order, tiling and record table the field launches need (host work
       // and allocation cannot be captured)

@@ -72,6 +72,8 @@ constexpr int kDefaultWindowRunNodes = 64;
 constexpr int kDefaultTileKB = 48;
 constexpr int kDefaultTileRows = 4;    // LDS tiles: rows per tile (band_rows)
 constexpr int kDefaultBatchClaim = 4;  // batched persistent form: tiles per work claim
+constexpr int64_t kBatchFieldValues = 5 << 22;   // batched plans: values per tracer from which field launches are the default
+constexpr int kBatchFieldCounts = 8;             // ... and the most different level counts (each has its own tables)
 constexpr int kDefaultTileSweep = 8;   // LDS tiles: bands swept together (run_nodes)
 inline int band_rows_of(const Shape& s) { return s.band_rows > 0 ? s.band_rows : kDefaultBandRows; }
 inline int run_nodes_of(const Shape& s) { return s.run_nodes > 0 ? s.run_nodes : kDefaultRunNodes; }
