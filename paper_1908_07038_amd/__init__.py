@@ -234,28 +234,45 @@ class NodeColumns:
 
 # ---- torch marshalling ------------------------------------------------------
 
+# The operators' entry points take addresses and streams as plain integers, and
+# what does not change between calls is looked up once: an O32 x 10 gradient is
+# bound by the host.
+_codes = None
+_raw_stream = None
+
+
 def _dtype_code(t):
-    import torch
-    codes = {torch.float64: F64, torch.float32: F32, torch.bfloat16: BF16}
-    if t.dtype not in codes:
+    global _codes
+    if _codes is None:
+        import torch
+        _codes = {torch.float64: F64, torch.float32: F32, torch.bfloat16: BF16}
+    code = _codes.get(t.dtype)
+    if code is None:
         raise TypeError(f"unsupported dtype {t.dtype} (float64, float32, bfloat16)")
-    return codes[t.dtype]
+    return code
 
 
 def _stream(t):
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    """The handle of the current stream of t's device."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        # the handle without a Stream object around it
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda index: torch.cuda.current_stream(index).cuda_stream)
+    return _raw_stream(t.get_device())
 
 
 def _field(mesh, t, comps, name):
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
+    shape = t.shape
     want = 3 if comps == 2 else 2
-    if t.dim() != want or t.shape[0] != mesh.nnodes or (comps == 2 and t.shape[2] != 2):
+    if len(shape) != want or shape[0] != mesh.nnodes or (comps == 2 and shape[2] != 2):
         raise ValueError(f"{name} must have shape [nnodes][nlev]" + ("[2]" if comps == 2 else ""))
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return t.shape[1]
+    return shape[1]
 
 
 def _like(mesh, t, comps, nlev, dtype, name):
@@ -276,8 +293,7 @@ def _apply(fn, mesh, x, in_comps, out_comps, out):
         out = torch.empty(shape, dtype=x.dtype, device=x.device)
     else:
         _like(mesh, out, out_comps, nlev, x.dtype, "out")
-    _check(fn(mesh.handle, _dtype_code(x), nlev, ctypes.c_void_p(x.data_ptr()),
-              ctypes.c_void_p(out.data_ptr()), _stream(x)))
+    _check(fn(mesh._h, _dtype_code(x), nlev, x.data_ptr(), out.data_ptr(), _stream(x)))
     return out
 
 
@@ -322,9 +338,9 @@ def laplacian(mesh, f, out=None, workspace=None):
         out = torch.empty_like(f)
     else:
         _like(mesh, out, 1, nlev, f.dtype, "out")
-    ws = ctypes.c_void_p(workspace.data_ptr()) if workspace is not None else None
-    _check(lib().atlas_nabla_laplacian(mesh.handle, _dtype_code(f), nlev, ctypes.c_void_p(f.data_ptr()),
-                                       ctypes.c_void_p(out.data_ptr()), ws, _stream(f)))
+    ws = workspace.data_ptr() if workspace is not None else None
+    _check(lib().atlas_nabla_laplacian(mesh.handle, _dtype_code(f), nlev, f.data_ptr(),
+                                       out.data_ptr(), ws, _stream(f)))
     return out
 
 
@@ -376,8 +392,8 @@ class Remap:
         elif (not out.is_cuda or out.dtype != f.dtype or tuple(out.shape) != (self.npoints, nlev)
               or not out.is_contiguous()):
             raise ValueError("out must be a contiguous device tensor [npoints][nlev] of the input dtype")
-        _check(lib().atlas_remap_apply(self._h, _dtype_code(f), nlev, ctypes.c_void_p(f.data_ptr()),
-                                       ctypes.c_void_p(out.data_ptr()), _stream(f)))
+        _check(lib().atlas_remap_apply(self._h, _dtype_code(f), nlev, f.data_ptr(),
+                                       out.data_ptr(), _stream(f)))
         return out
 
     def adjoint(self, ybar, out=None):
@@ -390,8 +406,8 @@ class Remap:
             out = torch.empty((self.mesh.nnodes, nlev), dtype=ybar.dtype, device=ybar.device)
         else:
             _like(self.mesh, out, 1, nlev, ybar.dtype, "out")
-        _check(lib().atlas_remap_apply_adjoint(self._h, _dtype_code(ybar), nlev, ctypes.c_void_p(ybar.data_ptr()),
-                                               ctypes.c_void_p(out.data_ptr()), _stream(ybar)))
+        _check(lib().atlas_remap_apply_adjoint(self._h, _dtype_code(ybar), nlev, ybar.data_ptr(),
+                                               out.data_ptr(), _stream(ybar)))
         return out
 
 
@@ -408,9 +424,9 @@ def gradient_laplacian(mesh, f, out_grad=None, out_lap=None):
         out_grad = torch.empty((mesh.nnodes, nlev, 2), dtype=f.dtype, device=f.device)
     if out_lap is None:
         out_lap = torch.empty_like(f)
-    _check(lib().atlas_nabla_gradient_laplacian(mesh.handle, _dtype_code(f), nlev, ctypes.c_void_p(f.data_ptr()),
-                                                ctypes.c_void_p(out_grad.data_ptr()),
-                                                ctypes.c_void_p(out_lap.data_ptr()), _stream(f)))
+    _check(lib().atlas_nabla_gradient_laplacian(mesh.handle, _dtype_code(f), nlev, f.data_ptr(),
+                                                out_grad.data_ptr(),
+                                                out_lap.data_ptr(), _stream(f)))
     return out_grad, out_lap
 
 
@@ -427,9 +443,9 @@ def divergence_curl(mesh, uv, out_div=None, out_curl=None):
         out_div = torch.empty((mesh.nnodes, nlev), dtype=uv.dtype, device=uv.device)
     if out_curl is None:
         out_curl = torch.empty((mesh.nnodes, nlev), dtype=uv.dtype, device=uv.device)
-    _check(lib().atlas_nabla_divergence_curl(mesh.handle, _dtype_code(uv), nlev, ctypes.c_void_p(uv.data_ptr()),
-                                             ctypes.c_void_p(out_div.data_ptr()),
-                                             ctypes.c_void_p(out_curl.data_ptr()), _stream(uv)))
+    _check(lib().atlas_nabla_divergence_curl(mesh.handle, _dtype_code(uv), nlev, uv.data_ptr(),
+                                             out_div.data_ptr(),
+                                             out_curl.data_ptr(), _stream(uv)))
     return out_div, out_curl
 
 
@@ -447,9 +463,9 @@ def divergence_gradient_adjoint(mesh, uv, out_div=None, out_fbar=None):
     if out_fbar is None:
         out_fbar = torch.empty((mesh.nnodes, nlev), dtype=uv.dtype, device=uv.device)
     _check(lib().atlas_nabla_divergence_gradient_adjoint(mesh.handle, _dtype_code(uv), nlev,
-                                                         ctypes.c_void_p(uv.data_ptr()),
-                                                         ctypes.c_void_p(out_div.data_ptr()),
-                                                         ctypes.c_void_p(out_fbar.data_ptr()), _stream(uv)))
+                                                         uv.data_ptr(),
+                                                         out_div.data_ptr(),
+                                                         out_fbar.data_ptr(), _stream(uv)))
     return out_div, out_fbar
 
 
@@ -459,8 +475,8 @@ def conservation(mesh, div):
     nlev = _field(mesh, div, 1, "div")
     s = torch.empty(nlev, dtype=torch.float64, device=div.device)
     a = torch.empty(nlev, dtype=torch.float64, device=div.device)
-    _check(lib().atlas_nabla_conservation(mesh.handle, _dtype_code(div), nlev, ctypes.c_void_p(div.data_ptr()),
-                                          ctypes.c_void_p(s.data_ptr()), ctypes.c_void_p(a.data_ptr()),
+    _check(lib().atlas_nabla_conservation(mesh.handle, _dtype_code(div), nlev, div.data_ptr(),
+                                          s.data_ptr(), a.data_ptr(),
                                           _stream(div)))
     return s, a
 
@@ -476,9 +492,9 @@ def conservation_noalloc(mesh, div, out_sum, out_abs):
                 and tuple(t.shape) == (nlev,) and t.is_contiguous()):
             raise ValueError(f"{name} must be a contiguous float64 tensor of shape ({nlev},) on {div.device}")
     _check(lib().atlas_nabla_conservation_noalloc(mesh.handle, _dtype_code(div), nlev,
-                                                  ctypes.c_void_p(div.data_ptr()),
-                                                  ctypes.c_void_p(out_sum.data_ptr()),
-                                                  ctypes.c_void_p(out_abs.data_ptr()), _stream(div)))
+                                                  div.data_ptr(),
+                                                  out_sum.data_ptr(),
+                                                  out_abs.data_ptr(), _stream(div)))
     return out_sum, out_abs
 
 
@@ -487,8 +503,8 @@ def tune(mesh, op, x, out, reps=10):
     best = TuneShape()
     ms = ctypes.c_float()
     nlev = x.shape[1]
-    _check(lib().atlas_nabla_tune(mesh.handle, _dtype_code(x), op, nlev, ctypes.c_void_p(x.data_ptr()),
-                                  ctypes.c_void_p(out.data_ptr()), reps, _stream(x), ctypes.byref(best),
+    _check(lib().atlas_nabla_tune(mesh.handle, _dtype_code(x), op, nlev, x.data_ptr(),
+                                  out.data_ptr(), reps, _stream(x), ctypes.byref(best),
                                   ctypes.byref(ms)))
     return best.as_dict(), ms.value
 

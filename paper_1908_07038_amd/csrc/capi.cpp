@@ -39,13 +39,14 @@ int hip_fail(hipError_t e, const char* what) {
 // caller's current device unchanged.
 struct DeviceGuard {
   int prev = -1;
+  int dev;
   bool ok = false;
-  explicit DeviceGuard(int dev) {
+  explicit DeviceGuard(int device) : dev(device) {
     if (hipGetDevice(&prev) != hipSuccess) prev = -1;
     ok = (prev == dev) || hipSetDevice(dev) == hipSuccess;
   }
   ~DeviceGuard() {
-    if (prev >= 0) (void)hipSetDevice(prev);
+    if (prev >= 0 && prev != dev) (void)hipSetDevice(prev);
   }
 };
 
