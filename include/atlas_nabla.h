@@ -180,6 +180,13 @@ int atlas_nabla_gradient_adjoint(atlas_mesh_t mesh, int dtype, int32_t nlev,
 int atlas_nabla_divergence_adjoint(atlas_mesh_t mesh, int dtype, int32_t nlev,
                                    const void* d, void* uvbar, void* stream);
 
+/* The divergence adjoint added to a field: uvbar = base + D^T d, where each
+ * sum is of the two fields' own values (D^T d rounded to the dtype first), in
+ * one pass on the one-tile LDS form.  base: vector [V][nlev][2], not
+ * overlapping uvbar. */
+int atlas_nabla_divergence_adjoint_add(atlas_mesh_t mesh, int dtype, int32_t nlev, const void* d,
+                                       const void* base, void* uvbar, void* stream);
+
 /* Curl (vertical vorticity), the fourth operation Section 2.3 names, in the
  * same edge-based form with the tangential face vector:
  * curl_i = (1/V_i) sum_e sign(i,e) 0.5 (U_i + U_j) . T_e, T_e = m_e x S_e,

@@ -83,6 +83,7 @@ _SIGS = {
     "atlas_nabla_laplacian": (ctypes.c_int, [_P, ctypes.c_int, _I32, _P, _P, _P, _P]),
     "atlas_nabla_gradient_adjoint": (ctypes.c_int, [_P, ctypes.c_int, _I32, _P, _P, _P]),
     "atlas_nabla_divergence_adjoint": (ctypes.c_int, [_P, ctypes.c_int, _I32, _P, _P, _P]),
+    "atlas_nabla_divergence_adjoint_add": (ctypes.c_int, [_P, ctypes.c_int, _I32, _P, _P, _P, _P]),
     "atlas_nabla_conservation": (ctypes.c_int, [_P, ctypes.c_int, _I32, _P, _P, _P, _P]),
     "atlas_nabla_conservation_noalloc": (ctypes.c_int, [_P, ctypes.c_int, _I32, _P, _P, _P, _P]),
     "atlas_nabla_gradient_laplacian": (ctypes.c_int, [_P, ctypes.c_int, _I32, _P, _P, _P, _P]),
@@ -315,6 +316,17 @@ def gradient_adjoint(mesh, w, out=None):
 def divergence_adjoint(mesh, d, out=None):
     """[V][L] -> [V][L][2], exact transpose of :func:`divergence`."""
     return _apply(lib().atlas_nabla_divergence_adjoint, mesh, d, 1, 2, out)
+
+
+def _divergence_adjoint_add(mesh, d, base):
+    """base + divergence_adjoint(d), in one pass on the LDS tiles."""
+    import torch
+    nlev = _field(mesh, d, 1, "input")
+    _like(mesh, base, 2, nlev, d.dtype, "base")
+    out = torch.empty_like(base)
+    _check(lib().atlas_nabla_divergence_adjoint_add(mesh.handle, _dtype_code(d), nlev, d.data_ptr(), base.data_ptr(),
+                                                    out.data_ptr(), _stream(d)))
+    return out
 
 
 def curl(mesh, uv, out=None):

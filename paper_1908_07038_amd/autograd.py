@@ -8,8 +8,8 @@ Laplacian L = D G has the adjoint G^T D^T.
 
 import torch
 
-from . import (curl, curl_adjoint, divergence, divergence_adjoint, divergence_curl, divergence_gradient_adjoint,
-               gradient, gradient_adjoint, gradient_laplacian, laplacian)
+from . import (_divergence_adjoint_add, curl, curl_adjoint, divergence, divergence_adjoint, divergence_curl,
+               divergence_gradient_adjoint, gradient, gradient_adjoint, gradient_laplacian, laplacian)
 
 
 class Gradient(torch.autograd.Function):
@@ -56,6 +56,16 @@ class Curl(torch.autograd.Function):
         return None, curl_adjoint(ctx.mesh, zbar.contiguous())
 
 
+def _add_divergence_adjoint(mesh, d, w):
+    """w + D^T d (D^T d for w None): one pass where w is a plain field of d's
+    type and aligned to its pairs, as the kernel's other fields are."""
+    if w is None:
+        return divergence_adjoint(mesh, d)
+    if w.dtype != d.dtype or w.data_ptr() % (2 * w.element_size()):
+        return w + divergence_adjoint(mesh, d)
+    return _divergence_adjoint_add(mesh, d, w)
+
+
 class GradientLaplacian(torch.autograd.Function):
     """(grad f, lap f) in one pass; backward G^T (gbar + D^T lbar)."""
 
@@ -68,8 +78,7 @@ class GradientLaplacian(torch.autograd.Function):
     def backward(ctx, gbar, lbar):
         w = gbar.contiguous() if gbar is not None else None
         if lbar is not None:
-            t = divergence_adjoint(ctx.mesh, lbar.contiguous())
-            w = t if w is None else w + t
+            w = _add_divergence_adjoint(ctx.mesh, lbar.contiguous(), w)
         return None, gradient_adjoint(ctx.mesh, w)
 
 
@@ -83,12 +92,9 @@ class DivergenceCurl(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, dbar, zbar):
-        out = None
+        out = curl_adjoint(ctx.mesh, zbar.contiguous()) if zbar is not None else None
         if dbar is not None:
-            out = divergence_adjoint(ctx.mesh, dbar.contiguous())
-        if zbar is not None:
-            t = curl_adjoint(ctx.mesh, zbar.contiguous())
-            out = t if out is None else out + t
+            out = _add_divergence_adjoint(ctx.mesh, dbar.contiguous(), out)
         return None, out
 
 
@@ -103,12 +109,9 @@ class DivergenceGradientAdjoint(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, dbar, fbar):
-        out = None
+        out = gradient(ctx.mesh, fbar.contiguous()) if fbar is not None else None
         if dbar is not None:
-            out = divergence_adjoint(ctx.mesh, dbar.contiguous())
-        if fbar is not None:
-            t = gradient(ctx.mesh, fbar.contiguous())
-            out = t if out is None else out + t
+            out = _add_divergence_adjoint(ctx.mesh, dbar.contiguous(), out)
         return None, out
 
 

@@ -373,9 +373,10 @@ int call_tiles(atlas_mesh_t mesh, int op, int dtype, TileGeom& tg, const Shape& 
 }
 
 // build: only build what the call needs on first use (tiles, records, node
-// order); nothing is launched.
+// order); nothing is launched.  add (OP_DIVT): a field of the output's form
+// that the result is added to.
 int run_op(atlas_mesh_t mesh, int op, int dtype, int32_t nlev, const void* in, void* out, void* stream,
-           const Shape* shape_override = nullptr, bool build = false) {
+           const Shape* shape_override = nullptr, bool build = false, const void* add = nullptr) {
   int rc = check_mesh_device(mesh);
   if (rc) return rc;
   const size_t es = dtype_size(dtype);
@@ -389,6 +390,8 @@ int run_op(atlas_mesh_t mesh, int op, int dtype, int32_t nlev, const void* in, v
   const size_t nin = (size_t)V * nlev * kInComps[op] * es;
   const size_t nout = (size_t)V * nlev * kOutComps[op] * es;
   if (overlaps(in, nin, out, nout)) return fail(ATLAS_EINVAL, "output overlaps input");
+  if (add && (rc = check_field(add, kOutComps[op], es, "base"))) return rc;
+  if (add && overlaps(add, nout, out, nout)) return fail(ATLAS_EINVAL, "output overlaps base");
   DeviceGuard g(mesh->device);
   if (!g.ok) return fail(ATLAS_EHIP, "cannot select the mesh's device");
   const Shape& asked = shape_override ? *shape_override : mesh->shape[op][dtype];
@@ -403,7 +406,10 @@ int run_op(atlas_mesh_t mesh, int op, int dtype, int32_t nlev, const void* in, v
   if (tg.KL > 0 && (rc = call_tiles(mesh, op, dtype, tg, sh, dt, rec, (hipStream_t)stream))) return rc;
   if (tg.KL > 0) {
     if (build) return ATLAS_OK;
-    hipError_t e = launch_tiles(op, dtype, dt, rec, nlev, in, out, sh, mesh->num_cus, (hipStream_t)stream);
+    const bool fused = add && sh.lds_tiles == 3;
+    hipError_t e = launch_tiles(op, dtype, dt, rec, nlev, in, out, sh, mesh->num_cus, (hipStream_t)stream,
+                                fused ? const_cast<void*>(add) : nullptr);
+    if (e == hipSuccess && add && !fused) e = launch_add(dtype, 2 * (int64_t)nlev * V, add, out, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, kOpName[op]);
     return ATLAS_OK;
   }
@@ -426,6 +432,7 @@ int run_op(atlas_mesh_t mesh, int op, int dtype, int32_t nlev, const void* in, v
   }
   if (build) return ATLAS_OK;
   hipError_t e = launch_op(op, dtype, mesh->tables(dtype), order, V, nlev, in, out, sh, (hipStream_t)stream);
+  if (e == hipSuccess && add) e = launch_add(dtype, 2 * (int64_t)nlev * V, add, out, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, kOpName[op]);
   return ATLAS_OK;
 }
@@ -568,6 +575,12 @@ int atlas_nabla_gradient_adjoint(atlas_mesh_t mesh, int dtype, int32_t nlev, con
 int atlas_nabla_divergence_adjoint(atlas_mesh_t mesh, int dtype, int32_t nlev, const void* d, void* uvbar,
                                    void* stream) {
   return run_op(mesh, OP_DIVT, dtype, nlev, d, uvbar, stream);
+}
+
+int atlas_nabla_divergence_adjoint_add(atlas_mesh_t mesh, int dtype, int32_t nlev, const void* d, const void* base,
+                                       void* uvbar, void* stream) {
+  if (!base) return fail(ATLAS_EINVAL, "base is NULL");
+  return run_op(mesh, OP_DIVT, dtype, nlev, d, uvbar, stream, nullptr, false, base);
 }
 
 int atlas_nabla_curl(atlas_mesh_t mesh, int dtype, int32_t nlev, const void* uv, void* zeta, void* stream) {

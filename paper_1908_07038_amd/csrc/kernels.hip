@@ -31,6 +31,7 @@
 // contiguous part of the order (whole bands) in its own L2.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <mutex>
 #include <type_traits>
@@ -325,6 +326,10 @@ __device__ __forceinline__ void run_group(const Args& a, int64_t gbase, int lane
 // slot.  Either way the values are combined in slot order with the same fused
 // multiply-adds as the per-lane path, so all paths give identical bits.
 
+// The operators of two output components.
+template <int OP>
+constexpr bool kTwoOut = OP == OP_GRAD || OP == OP_DIVT || OP == OP_DIVTA;
+
 template <class S, int OP>
 struct WinT {
   using C = typename Traits<S>::C;
@@ -344,7 +349,7 @@ __device__ __forceinline__ void win_combine(const typename WinT<S, OP>::X x0, co
                                             const typename Traits<S>::C2* cf, typename Traits<S>::C2 dg,
                                             typename Traits<S>::C& r0, typename Traits<S>::C& r1) {
   using C = typename Traits<S>::C;
-  if constexpr (OP == OP_GRAD || OP == OP_DIVT) {
+  if constexpr (kTwoOut<OP>) {
     C ax, ay;
     if constexpr (OP == OP_GRAD) {
       ax = 0;
@@ -384,7 +389,7 @@ __device__ __forceinline__ void win_combine(const typename WinT<S, OP>::X x0, co
 template <class S, int OP>
 __device__ __forceinline__ void win_store(S* __restrict__ out, uint32_t o, int nt, typename Traits<S>::C r0,
                                           typename Traits<S>::C r1) {
-  if constexpr (OP == OP_GRAD || OP == OP_DIVT) {
+  if constexpr (kTwoOut<OP>) {
     if (nt) st2<true>(out + 2 * (size_t)o, r0, r1);
     else st2<false>(out + 2 * (size_t)o, r0, r1);
   } else {
@@ -621,7 +626,7 @@ struct TileArgs {
   const char* rec;       // [V] node records in tile order (see tile_record_bytes)
   const void* in;
   void* out;
-  void* out2;            // OP_GRADLAP: the gradient ([V][L][2]); out gets the Laplacian
+  void* out2;            // OP_GRADLAP: the gradient ([V][L][2]); out gets the Laplacian; OP_DIVTA: the addend (read)
   int64_t ntiles;
   int32_t L;             // levels
   int32_t KL;            // levels per chunk (L: whole columns)
@@ -630,6 +635,28 @@ struct TileArgs {
 };
 
 namespace {
+
+// win_store of a tile's value; OP_DIVTA: plus the addend at the same place,
+// after the rounding to the field's type that storing it would make.
+// Bound by memory like the divergence adjoint itself: the addend is read once
+// where the sum as a pass of its own reads two fields and writes one (backward
+// of the one-pass gradient and Laplacian with its forward, O320 x 60 FP32: 379
+// -> 312 us).
+template <class S, int OP>
+__device__ __forceinline__ void tile_store(const TileArgs& a, S* __restrict__ out, uint32_t o, typename Traits<S>::C r0,
+                                           typename Traits<S>::C r1) {
+  if constexpr (OP == OP_DIVTA) {
+    const S* add = static_cast<const S*>(a.out2) + ((out + 2 * (size_t)o) - static_cast<S*>(a.out));
+    const typename Traits<S>::C2 b = ld2(add);
+    if constexpr (sizeof(S) == 2) {
+      r0 = bf16_to_f32(f32_to_bf16(r0));
+      r1 = bf16_to_f32(f32_to_bf16(r1));
+    }
+    r0 += b.x;
+    r1 += b.y;
+  }
+  win_store<S, OP>(out, o, a.nt, r0, r1);
+}
 
 // Node record of the tile path: coefficient row (8 pairs, ring 1, followed
 // for OP_DIVCURL by the 8 pairs of the second operator, the curl's or, for
@@ -799,7 +826,7 @@ __device__ __forceinline__ void tile_node1(const TileArgs& a, const char* lds, c
   using C = typename Traits<S>::C;
   using R = TileRec<S, OP>;
   constexpr uint32_t kEl = (uint32_t)sizeof(S) * R::kCin;   // bytes per level in LDS
-  constexpr uint32_t kOut = (OP == OP_GRAD || OP == OP_DIVT) ? 2 : 1;
+  constexpr uint32_t kOut = kTwoOut<OP> ? 2 : 1;
   // BF16: values are left to the compiler's placement, which keeps the
   // vector-input kernels within 64 VGPRs (four workgroups per CU)
   constexpr bool kKeep = sizeof(S) != 2;
@@ -829,7 +856,7 @@ __device__ __forceinline__ void tile_node1(const TileArgs& a, const char* lds, c
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (kb + 64 * u + lane < klc) win_store<S, OP>(out + (size_t)kOut * kb, 64u * u, a.nt, r0[u], r1[u]);
+      if (kb + 64 * u + lane < klc) tile_store<S, OP>(a, out + (size_t)kOut * kb, 64u * u, r0[u], r1[u]);
   };
   step(0);
   for (int kb = 64 * U; kb < klc; kb += 64 * U) step(kb);
@@ -1169,7 +1196,7 @@ __device__ __forceinline__ void tile_block(const TileArgs& a, const char* lds, i
   using X = typename WinT<S, R::kRing2 ? (int)OP_GRAD : OP>::X;
   constexpr int U = UT < kBlkU<S, OP> ? UT : kBlkU<S, OP>;
   constexpr uint32_t kEl = (uint32_t)sizeof(S) * R::kCin;
-  constexpr uint32_t kOut = (OP == OP_GRAD || OP == OP_DIVT) ? 2 : 1;
+  constexpr uint32_t kOut = kTwoOut<OP> ? 2 : 1;
   constexpr int ring = R::kRing2 ? 2 : 1;
   const uint32_t ro = (uint32_t)r0 * R::kBytes;
   const uint32_t obase = uni((uint32_t)lds_ld<int32_t>(lds, ro + R::kIdOff)) * (uint32_t)a.L + (uint32_t)k0;
@@ -1216,7 +1243,7 @@ __device__ __forceinline__ void tile_block(const TileArgs& a, const char* lds, i
             if (a.nt) st1<true>(out + o, r[u]);
             else st1<false>(out + o, r[u]);
           } else {
-            win_store<S, OP>(out, o, a.nt, r[u], q[u]);
+            tile_store<S, OP>(a, out, o, r[u], q[u]);
             if constexpr (R::kDual) win_store<S, OP>(out2, o, a.nt, z[u], 0);
           }
         }
@@ -1336,7 +1363,7 @@ __device__ __forceinline__ void tile_block(const TileArgs& a, const char* lds, i
       combine(0, r0, r1);
       if constexpr (R::kDual) combine(8 * (uint32_t)sizeof(C2), z0, unused);
       if (ok) {
-        win_store<S, OP>(o1, 0, a.nt, r0, r1);
+        tile_store<S, OP>(a, o1, 0, r0, r1);
         if constexpr (R::kDual) win_store<S, OP>(static_cast<S*>(a.out2) + o, 0, a.nt, z0, 0);
       }
     } else {
@@ -1481,7 +1508,7 @@ __device__ __forceinline__ void tile_tail(const TileArgs& a, const char* lds, in
         combine(8 * (uint32_t)sizeof(C2), z0, z1);
         if (ok) win_store<S, OP>(static_cast<S*>(a.out2), o, a.nt, z0, z1);
       }
-      if (ok) win_store<S, OP>(out, o, a.nt, r0, r1);
+      if (ok) tile_store<S, OP>(a, out, o, r0, r1);
     }
   }
 }
@@ -1500,7 +1527,7 @@ __device__ __forceinline__ void tile_short(const TileArgs& a, const char* lds, i
   using C2 = typename Traits<S>::C2;
   using X = typename WinT<S, R::kRing2 ? (int)OP_GRAD : OP>::X;
   constexpr uint32_t kEl = (uint32_t)sizeof(S) * R::kCin;
-  constexpr uint32_t kOut = (OP == OP_GRAD || OP == OP_DIVT) ? 2 : 1;
+  constexpr uint32_t kOut = kTwoOut<OP> ? 2 : 1;
   constexpr int ring = R::kRing2 ? 2 : 1;
   const int G = 64 / rem;
   for (int32_t g0 = wave * G; g0 < nblk; g0 += W * G) {
@@ -1546,7 +1573,7 @@ __device__ __forceinline__ void tile_short(const TileArgs& a, const char* lds, i
         if constexpr (R::kDual) combine(8 * (uint32_t)sizeof(C2), z0, unused);
         if (ok) {
           const size_t o = (size_t)(o0 + (uint32_t)(b * a.L));
-          win_store<S, OP>(static_cast<S*>(a.out) + kOut * o, 0, a.nt, r0, r1);
+          tile_store<S, OP>(a, static_cast<S*>(a.out) + kOut * o, 0, r0, r1);
           if constexpr (R::kDual) win_store<S, OP>(static_cast<S*>(a.out2) + o, 0, a.nt, z0, 0);
         }
       }
@@ -2427,6 +2454,14 @@ hipError_t launch_remap_adj_t(const int64_t* off, const int32_t* tt, const void*
   return launch_remap_adj_ns<S, 9, 1>(off, tt, w, ht, hw, V, P, nlev, lanes, src, dst, st);
 }
 
+// out += base over n numbers, for divergence adjoints with an addend off the
+// LDS tiles.
+template <class S>
+__global__ __launch_bounds__(256) void k_add(const S* __restrict__ base, S* __restrict__ out, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+    st1<false>(out + i, ld1(out + i) + ld1(base + i));
+}
+
 // ---- conservation: fixed-order FP64 sums of V_i div_ik --------------------------
 //
 // Workgroup b reduces nodes [b*chunk, (b+1)*chunk) for every level.  Wave w
@@ -2822,7 +2857,9 @@ hipError_t launch_tiles_t(int op, const TileArgs& a, int U, uint32_t lds, const 
     case OP_GRAD: return launch_tile_u<S, OP_GRAD>(a, U, g, b, lds, nblocks, sh.xcd_remap, st);
     case OP_DIV: return launch_tile_u<S, OP_DIV>(a, U, g, b, lds, nblocks, sh.xcd_remap, st);
     case OP_GRADT: return launch_tile_u<S, OP_GRADT>(a, U, g, b, lds, nblocks, sh.xcd_remap, st);
-    case OP_DIVT: return launch_tile_u<S, OP_DIVT>(a, U, g, b, lds, nblocks, sh.xcd_remap, st);
+    case OP_DIVT:
+      if (a.out2) return launch_tile_u<S, OP_DIVTA>(a, U, g, b, lds, nblocks, sh.xcd_remap, st);
+      return launch_tile_u<S, OP_DIVT>(a, U, g, b, lds, nblocks, sh.xcd_remap, st);
     case OP_LAP: return launch_tile_u<S, OP_LAP>(a, U, g, b, lds, nblocks, sh.xcd_remap, st);
     case OP_GRADLAP: return launch_tile_u<S, OP_GRADLAP>(a, U, g, b, lds, nblocks, sh.xcd_remap, st);
     case OP_DIVCURL: return launch_tile_u<S, OP_DIVCURL>(a, U, g, b, lds, nblocks, sh.xcd_remap, st);
@@ -3206,7 +3243,8 @@ hipError_t launch_tiles(int op, int dtype, const DevTiles& dt, const void* rec, 
   a.out = out;
   a.out2 = out2;
   const bool two = op == OP_GRADLAP || kernel_op(op) == OP_DIVCURL;
-  if (two != (out2 != nullptr) || (two && shape.lds_tiles != 3))
+  const bool second = two || (kernel_op(op) == OP_DIVT && out2);   // with an addend
+  if (second != (out2 != nullptr) || (second && shape.lds_tiles != 3))
     return hipErrorInvalidValue;   // the one-pass forms: one-tile workgroups, both outputs
   a.ntiles = dt.ntiles;
   if (shape.lds_tiles == 3 && shape.xcd_remap == kXcdSchedule) {
@@ -3287,6 +3325,18 @@ int window_slices(int nlev, const Shape& sh) {
   int U = sh.slices_per_iter > 0 ? sh.slices_per_iter : 3;
   if (U > 3) U = 3;
   return U < nsl ? U : nsl;
+}
+
+hipError_t launch_add(int dtype, int64_t n, const void* base, void* out, hipStream_t st) {
+  const dim3 g((unsigned)std::min<int64_t>((n + 255) / 256, 65536)), b(256);
+  if (dtype == DT_F64)
+    hipLaunchKernelGGL((k_add<double>), g, b, 0, st, static_cast<const double*>(base), static_cast<double*>(out), n);
+  else if (dtype == DT_F32)
+    hipLaunchKernelGGL((k_add<float>), g, b, 0, st, static_cast<const float*>(base), static_cast<float*>(out), n);
+  else if (dtype == DT_BF16)
+    hipLaunchKernelGGL((k_add<bf16_t>), g, b, 0, st, static_cast<const bf16_t*>(base), static_cast<bf16_t*>(out), n);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 int conservation_parts(int64_t V, int nlev) {

@@ -22,6 +22,9 @@ constexpr int OP_DIVCURL = OP_COUNT + 1;
 // coefficient rows (both operators combine a vector field's 1-ring values
 // with a diagonal and one pair per slot, in slot order).
 constexpr int OP_DIVGRADT = OP_COUNT + 2;
+// Divergence adjoint added to a field of its output's form (one-tile form
+// only; launch_tiles takes it where an addend is given).
+constexpr int OP_DIVTA = OP_COUNT + 3;
 // Kernel template an operator runs with.
 inline int kernel_op(int op) {
   return op == OP_CURL ? OP_DIV : op == OP_CURLT ? OP_DIVT : op == OP_DIVGRADT ? OP_DIVCURL : op;
@@ -156,6 +159,9 @@ hipError_t launch_op(int op, int dtype, const DevTables& t, const NodeOrder& ord
 
 // Conservation sums: partial [nparts][nlev][2] doubles of scratch, then the
 // final fixed-order pass into out_sum/out_abs.
+// out += base (n numbers; BF16 in FP32, rounded once).
+hipError_t launch_add(int dtype, int64_t n, const void* base, void* out, hipStream_t stream);
+
 int conservation_parts(int64_t V, int nlev);
 hipError_t launch_conservation(int dtype, const double* vol, int64_t V, int nlev,
                                const void* div, double* scratch, double* out_sum,
