@@ -61,7 +61,7 @@ def _add_divergence_adjoint(mesh, d, w):
     type and aligned to its pairs, as the kernel's other fields are."""
     if w is None:
         return divergence_adjoint(mesh, d)
-    if w.dtype != d.dtype or w.data_ptr() % (2 * w.element_size()):
+    if w.dtype != d.dtype or w.is_neg() or w.data_ptr() % (2 * w.element_size()):
         return w + divergence_adjoint(mesh, d)
     return _divergence_adjoint_add(mesh, d, w)
 

@@ -12,7 +12,6 @@
 #include <cstring>
 #include <mutex>
 #include <new>
-#include <set>
 #include <stdexcept>
 #include <string>
 #include <vector>
@@ -349,15 +348,15 @@ int check_shape(Shape& s, const atlas_tune_t* t) {
 // nothing of its own.
 int call_tiles(atlas_mesh_t mesh, int op, int dtype, TileGeom& tg, const Shape& sh, DevTiles& dt, const void*& rec,
                hipStream_t stream) {
-  if (sh.short_tiles && !mesh->tiles_ready(tg, sh, op, dtype)) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &st) != hipSuccess) (void)hipGetLastError();
-    if (st != hipStreamCaptureStatusNone) {
-      tg.KL = 0;
-      return ATLAS_OK;
-    }
-  }
   try {
+    if (sh.short_tiles && !mesh->tiles_ready(tg, sh, op, dtype)) {
+      hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+      if (hipStreamIsCapturing(stream, &st) != hipSuccess) (void)hipGetLastError();
+      if (st != hipStreamCaptureStatusNone) {
+        tg.KL = 0;
+        return ATLAS_OK;
+      }
+    }
     // tilings depend on the byte sizes only; the level chunk is the call's
     dt = mesh->tiles(tg, sh);
     dt.KL = tg.KL;
@@ -1189,14 +1188,15 @@ bool plan_persistent(const Shape& sh) { return sh.batch_mode != 2; }
 // count has tilings and records of its own, which bounds the different ones.
 bool plan_fields(const atlas_batch_s* b) {
   int64_t levels = 0;
-  std::set<int32_t> counts;
+  int32_t counts[kBatchFieldCounts];
+  int n = 0;
   for (const atlas_tracer_desc_t& d : b->descs) {
     levels += d.nlev;
-    counts.insert(d.nlev);
+    if (std::find(counts, counts + n, d.nlev) != counts + n) continue;
+    if (n == kBatchFieldCounts) return false;
+    counts[n++] = d.nlev;
   }
-  if (b->mesh->host.V * levels < kBatchFieldValues * (int64_t)b->descs.size() ||
-      counts.size() > (size_t)kBatchFieldCounts)
-    return false;
+  if (b->mesh->host.V * levels < kBatchFieldValues * (int64_t)b->descs.size()) return false;
   atlas_tune_t def{};
   shape_out(Shape(), &def);
   for (int o = 0; o < 4; ++o) {

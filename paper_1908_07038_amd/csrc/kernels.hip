@@ -1657,7 +1657,11 @@ __device__ __forceinline__ void lds_barrier() {
 // One (tile, level chunk) of a field by the W waves of a workgroup: copy into
 // LDS, wait, run after_copy() (all waves are past the barrier), evaluate.
 // The caller synchronises before the buffer is reused.
-template <class S, int OP, int U, class F>
+// SHORT: every chunk is of at most 32 levels (U 1, types and operators with
+// blocks); a body of its own, since tile_short next to tile_block raises the
+// register count of the long columns' kernels (FP64 gradient and Laplacian at
+// O1280 x 137 7.1 -> 8.4 ms, BF16 divergence at O640 x 137 430 -> 523 us).
+template <class S, int OP, int U, bool SHORT, class F>
 __device__ __forceinline__ void tile_work(const TileArgs& a, int64_t tile, int chunk, char* lds, int W, int wave,
                                           int lane, F&& after_copy) {
   using R = TileRec<S, OP>;
@@ -1681,7 +1685,10 @@ __device__ __forceinline__ void tile_work(const TileArgs& a, int64_t tile, int c
     constexpr int NB = kBlkN<S, OP>;
     const int tj = pack ? lane / rem : 0, tt = pack ? lane - tj * rem : 0;   // packed pass: node and level of the lane
     int32_t n0 = 0, q = wave;
-    if (kmain > 0) {
+    if constexpr (SHORT) {
+      n0 = nblk * NB;
+      tile_short<S, OP, NB>(a, lds, nblk, data_off, colB, k0, rem, tj, tt, wave, W);
+    } else if (kmain > 0) {
       n0 = nblk * NB;
       for (; q < nblk; q += W)
         tile_block<S, OP, U, NB>(a, lds, q * NB, data_off, colB, k0, kmain, pack ? rem : 0, tj, tt, lane);
@@ -1689,9 +1696,6 @@ __device__ __forceinline__ void tile_work(const TileArgs& a, int64_t tile, int c
       // the few nodes outside the blocks: one slice at a time, which keeps
       // them from setting the kernel's register count
       for (int32_t tn = n0 + q; tn < nnodes; tn += W) tile_eval<S, OP, 1>(a, lds, tn, data_off, colB, k0, kmain, lane);
-    } else {
-      n0 = nblk * NB;
-      tile_short<S, OP, NB>(a, lds, nblk, data_off, colB, k0, rem, tj, tt, wave, W);
     }
     if (pack) tile_tail<S, OP>(a, lds, nnodes, data_off, colB, k0, kmain, rem, tj, tt, n0, q, W, lane);
   } else {
@@ -1704,6 +1708,7 @@ __device__ __forceinline__ void tile_work(const TileArgs& a, int64_t tile, int c
   }
 }
 
+// U: 64-level slices per step; 0: columns of at most 32 levels (see tile_work).
 template <class S, int OP, int U>
 __global__ __launch_bounds__((kTileThreads<S, OP, U>), (kTileMinWaves<S, OP, U>)) void k_tile(TileArgs a, int64_t nblocks, int remap) {
   extern __shared__ __align__(16) char lds[];
@@ -1725,7 +1730,7 @@ __global__ __launch_bounds__((kTileThreads<S, OP, U>), (kTileMinWaves<S, OP, U>)
   const int W = blockDim.x >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  tile_work<S, OP, U>(a, tile, chunk, lds, W, wave, lane, [] {});
+  tile_work<S, OP, (U ? U : 1), U == 0>(a, tile, chunk, lds, W, wave, lane, [] {});
 }
 
 // Persistent form over many fields (tracers) of one operator, each on its
@@ -1831,9 +1836,11 @@ __global__ __launch_bounds__((kBatchedThreads<S, OP>)) void k_tile_batched(TileA
     };
     // UMAX: the largest slice count of the plan's tracers; only the paths
     // up to it are compiled in, which keeps the kernel's code small
-    if (UMAX == 1 || U == 1) tile_work<S, OP, 1>(a, tile, chunk, lds, W, wave, lane, advance);
-    else if (UMAX == 2 || U == 2) tile_work<S, OP, (UMAX < 2 ? UMAX : 2)>(a, tile, chunk, lds, W, wave, lane, advance);
-    else tile_work<S, OP, UMAX>(a, tile, chunk, lds, W, wave, lane, advance);
+    constexpr bool kShort = kUseBlk<S, OP, 1>;
+    if (kShort && a.KL <= 32) tile_work<S, OP, 1, kShort>(a, tile, chunk, lds, W, wave, lane, advance);
+    else if (UMAX == 1 || U == 1) tile_work<S, OP, 1, false>(a, tile, chunk, lds, W, wave, lane, advance);
+    else if (UMAX == 2 || U == 2) tile_work<S, OP, (UMAX < 2 ? UMAX : 2), false>(a, tile, chunk, lds, W, wave, lane, advance);
+    else tile_work<S, OP, UMAX, false>(a, tile, chunk, lds, W, wave, lane, advance);
     // every wave is done reading the buffer, and next_item is written; the
     // tile's output stores need not have landed
     lds_barrier();
@@ -2736,6 +2743,18 @@ hipError_t launch_u(const Args& a, int U, dim3 g, dim3 b, int64_t nblocks, int r
 template <class S, int OP>
 hipError_t launch_tile_u(const TileArgs& a, int U, dim3 g, dim3 b, uint32_t lds, int64_t nblocks, int remap,
                          hipStream_t st) {
+  if constexpr (kUseBlk<S, OP, 1>) {
+    if (a.KL <= 32) {
+      const void* fn = reinterpret_cast<const void*>(&k_tile<S, OP, 0>);
+      if ((int)b.x > kTileThreads<S, OP, 0>) b.x = kTileThreads<S, OP, 0>;
+      if (lds > 65536) {
+        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+      }
+      hipLaunchKernelGGL((k_tile<S, OP, 0>), g, b, lds, st, a, nblocks, remap);
+      return hipGetLastError();
+    }
+  }
   const int maxt = U == 1 ? kTileThreads<S, OP, 1> : U == 2 ? kTileThreads<S, OP, 2> : kTileThreads<S, OP, 3>;
   if ((int)b.x > maxt) b.x = (unsigned)maxt;
   if (lds > 65536) {
