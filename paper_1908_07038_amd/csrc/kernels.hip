@@ -1163,6 +1163,7 @@ __device__ __forceinline__ void tile_eval(const TileArgs& a, const char* lds, in
 // block's columns leave no room for both coefficient rows.
 template <class S, int OP>
 constexpr int kBlkN = OP == OP_DIVCURL               ? (sizeof(S) == 4 ? 0 : 2)
+                      : sizeof(S) == 8 && OP == OP_GRADLAP ? 2
                       : sizeof(S) == 4 && OP == OP_LAP ? 4
                       : sizeof(S) == 2 && TileRec<S, OP>::kCin == 2 ? 2 : 3;
 template <class S, int OP>
@@ -3058,7 +3059,7 @@ Shape resolve_path(int op, int dtype, int nlev, int64_t V, const Shape& sh) {
   if (op == OP_GRADLAP && dtype == DT_F64 && !e.slices_per_iter) e.slices_per_iter = 1;
   // one band of rows at a time, around the whole latitude circle (see
   // resolve_shape)
-  if (!e.run_nodes) e.run_nodes = 1;
+  if (!e.run_nodes) e.run_nodes = op == OP_GRADLAP && dtype == DT_F64 ? kDefaultTileSweep : 1;
   return e;
 }
 
@@ -3079,17 +3080,22 @@ Shape resolve_path(int op, int dtype, int nlev, int64_t V, const Shape& sh) {
 // Within a band each XCD takes an eighth of the longitude (schedule_tiles),
 // so tiles side by side share their halo columns in one L2, where that halo
 // is wide: two columns each side (the two-ring operators: FP32 Laplacian 580
-// -> 553 us, gradient and Laplacian 915 -> 872, FP64 1.88 -> 1.84 ms) or two
+// -> 553 us, gradient and Laplacian 915 -> 872) or two
 // components (divergence 599 -> 571 us FP32, 1.35 -> 1.31 ms FP64).  The
 // scalar-input 1-ring operators lose by it (FP64 gradient 1.10 -> 1.15 ms), so
 // do most BF16 columns, half as wide (gradient 330 -> 344 us, divergence and
 // curl 368 -> 382 at 91 levels): they keep the plain order.
+// The FP64 one-pass gradient and Laplacian, one 160 KiB tile per CU, keeps the
+// eighths and 8-band sweeps: O640 x 137 1837 us against 1931 with the schedule
+// and 1984 in plain order (all with its blocks of two nodes; x 60 827 against
+// 837 and 924).
 // The other paths, without a tile's reuse of its own halo, keep the eighths.
 Shape resolve_shape(int op, int dtype, int nlev, int64_t V, const Shape& sh) {
   Shape e = resolve_path(op, dtype, nlev, V, sh);
   if (e.xcd_remap >= 0) return e;
   const int k = kernel_op(op);
   if (!(e.lds_tiles == 3 && uses_tiles(op, dtype, nlev, e))) e.xcd_remap = 1;
+  else if (op == OP_GRADLAP && dtype == DT_F64) e.xcd_remap = 1;
   else e.xcd_remap = k == OP_GRAD || k == OP_DIVT || dtype == DT_BF16 ? 0 : kXcdSchedule;
   return e;
 }
