@@ -817,7 +817,7 @@ __device__ __forceinline__ void keep(T& v) {
 // Each lane's LDS address of a slot is formed once per node; the level slices
 // of a step then sit at constant offsets from it.  Lanes past the chunk's
 // last level read (and drop) values beyond their column, which stay inside
-// the tile buffer's tail of 64 U levels (tile_tail_bytes).
+// the tail behind the tile buffer (tile_tail_bytes).
 template <class S, int OP, int U, int DEG>
 __device__ __forceinline__ void tile_node1(const TileArgs& a, const char* lds, const uint32_t* so, uint32_t xo,
                                            const typename Traits<S>::C2* cf, typename Traits<S>::C2 dg,
@@ -3180,25 +3180,52 @@ int tile_slices(int KL, const Shape& sh) {
   return u < nsl ? u : nsl;
 }
 
-int64_t tile_tail_bytes(int op, int dtype, int KL, int nlev, int U) {
+int64_t tile_tail_bytes(int op, int dtype, int KL, int nlev, int U, bool one_tile) {
   const int64_t es = dtype == DT_F64 ? 8 : dtype == DT_BF16 ? 2 : 4;
   const int64_t cin = (kernel_op(op) == OP_DIV || kernel_op(op) == OP_GRADT || kernel_op(op) == OP_DIVCURL) ? 2 : 1;
-  // a step reads 64 U levels (64 on the single-slice paths) from level 0 on:
-  // past a chunk of k levels up to round_up(k, 64 U) - k levels
-  const int64_t step = 64 * (int64_t)U;
+  // a step reads 64 levels a slice (U slices, blocks at most kBlkU, other nodes
+  // down to one) from level 0 on, in the one-tile form without the levels of
+  // the packed pass
+  const int64_t step = 64 * (int64_t)(one_tile ? tile_step_slices(op, dtype, U) : U);
+  auto past = [&](int64_t k) -> int64_t {
+    const int64_t rem = k & 63, kmain = one_tile && rem != 0 && rem <= 32 ? k - rem : k;
+    const int64_t end = (kmain + step - 1) / step * step;
+    return end > k ? end - k : 0;
+  };
   const int64_t last = nlev - (int64_t)((nlev - 1) / KL) * KL;
-  const int64_t t0 = (KL + step - 1) / step * step - KL, t1 = (last + step - 1) / step * step - last;
+  const int64_t t0 = past(KL), t1 = past(last);
   return (t0 > t1 ? t0 : t1) * cin * es;
 }
 
-int tile_block_nodes(int op, int dtype) {
-  const bool dual = kernel_op(op) == OP_DIVCURL;
-  const bool vec = kernel_op(op) == OP_DIV || kernel_op(op) == OP_GRADT;
-  auto pick = [&](auto tag) {
-    using S = decltype(tag);
-    return op == OP_LAP ? kBlkN<S, OP_LAP> : op == OP_GRADLAP ? kBlkN<S, OP_GRADLAP> : dual ? kBlkN<S, OP_DIVCURL> : vec ? kBlkN<S, OP_DIV> : kBlkN<S, OP_GRAD>;
+// f(element type, kernel operator's tag): the block constants of an operator.
+namespace {
+template <class F>
+int with_block_op(int op, int dtype, F&& f) {
+  auto pick = [&](auto tag) -> int {
+    switch (kernel_op(op)) {
+      case OP_LAP: return f(tag, std::integral_constant<int, OP_LAP>());
+      case OP_GRADLAP: return f(tag, std::integral_constant<int, OP_GRADLAP>());
+      case OP_DIVCURL: return f(tag, std::integral_constant<int, OP_DIVCURL>());
+      case OP_DIV:
+      case OP_GRADT: return f(tag, std::integral_constant<int, OP_DIV>());
+      default: return f(tag, std::integral_constant<int, OP_GRAD>());
+    }
   };
   return dtype == DT_F64 ? pick(double()) : dtype == DT_F32 ? pick(float()) : pick(bf16_t());
+}
+}  // namespace
+
+int tile_step_slices(int op, int dtype, int U) {
+  return with_block_op(op, dtype, [&](auto tag, auto k) -> int {
+    using S = decltype(tag);
+    constexpr int OP = decltype(k)::value;
+    const bool blocks = U > 1 ? kUseBlk<S, OP, 2> : kUseBlk<S, OP, 1>;
+    return blocks && U > kBlkU<S, OP> ? kBlkU<S, OP> : U;
+  });
+}
+
+int tile_block_nodes(int op, int dtype) {
+  return with_block_op(op, dtype, [](auto tag, auto k) -> int { return kBlkN<decltype(tag), decltype(k)::value>; });
 }
 
 int64_t tile_record_bytes(int op, int dtype) {
@@ -3299,7 +3326,7 @@ hipError_t launch_tiles(int op, int dtype, const DevTiles& dt, const void* rec, 
   int U = shape.slices_per_iter > 0 ? shape.slices_per_iter : 3;
   if (U > nsl) U = nsl;
   // whole-wave nodes read past a column's last level, as in the one-tile form
-  const uint32_t lds = 2 * buf_bytes + (P == 64 ? (uint32_t)tile_tail_bytes(op, dtype, dt.KL, nlev, U) : 0u);
+  const uint32_t lds = 2 * buf_bytes + (P == 64 ? (uint32_t)tile_tail_bytes(op, dtype, dt.KL, nlev, U, false) : 0u);
   // workgroups per CU as asked, as far as their two buffers fit the CU's LDS
   int per_cu = shape.tile_wgs_per_cu > 0 ? shape.tile_wgs_per_cu : 1;
   while (per_cu > 1 && (uint64_t)lds * per_cu > kLdsPerCu) --per_cu;

@@ -133,11 +133,15 @@ TileGeom tile_geom(int op, int dtype, int nlev, const Shape& sh);
 int64_t tile_record_bytes(int op, int dtype);
 // Nodes a wave evaluates together where their stencils have the regular shape.
 int tile_block_nodes(int op, int dtype);
-// LDS bytes kept free behind a one-tile-per-workgroup buffer: lanes past a
-// column's last level read (and drop) values beyond it, up to the next
-// multiple of 64 U levels of a chunk (chunks of KL levels, the last one
-// shorter; U slices per step).
-int64_t tile_tail_bytes(int op, int dtype, int KL, int nlev, int U);
+// Slices of 64 levels the longest step of the one-tile form reads at a time
+// when launched with U of them: blocks take fewer than U.
+int tile_step_slices(int op, int dtype, int U);
+// LDS bytes kept free behind a workgroup's tile buffers: lanes past a column's
+// last level read (and drop) values beyond it, up to the end of the step
+// (chunks of KL levels, the last one shorter; U slices a step; one_tile: the
+// one-tile and batched forms, whose blocks step over tile_step_slices and
+// whose packed pass reads no further than the column).
+int64_t tile_tail_bytes(int op, int dtype, int KL, int nlev, int U, bool one_tile = true);
 // Level slices per step of the one-tile form for chunks of KL levels: the
 // whole 64-level slices (a remainder of 1..32 levels is evaluated in a packed
 // pass, several nodes to a wave), at most 3 or slices_per_iter.
