@@ -12,6 +12,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <set>
 #include <stdexcept>
 #include <string>
 #include <vector>
@@ -58,13 +59,75 @@ size_t dtype_size(int dtype) {
   }
 }
 
+// Device allocations that are freed together.
+struct DeviceMem {
+  std::vector<void*> blocks;
+
+  DeviceMem() = default;
+  DeviceMem(DeviceMem&& o) noexcept : blocks(std::move(o.blocks)) { o.blocks.clear(); }
+  DeviceMem& operator=(DeviceMem&& o) noexcept {
+    std::swap(blocks, o.blocks);
+    return *this;
+  }
+  ~DeviceMem() { release(); }
+
+  void release() {
+    for (void* p : blocks) (void)hipFree(p);
+    blocks.clear();
+  }
+  void* alloc(size_t bytes) {
+    blocks.reserve(blocks.size() + 1);
+    void* p = nullptr;
+    if (hipMalloc(&p, bytes ? bytes : 16) != hipSuccess) {
+      (void)hipGetLastError();
+      throw std::bad_alloc();
+    }
+    blocks.push_back(p);
+    return p;
+  }
+  template <class T>
+  T* upload(const std::vector<T>& v) {
+    const size_t bytes = v.size() * sizeof(T);
+    void* p = alloc(bytes);
+    if (bytes) {
+      const hipError_t e = hipMemcpy(p, v.data(), bytes, hipMemcpyHostToDevice);
+      if (e != hipSuccess) throw std::runtime_error(std::string("hipMemcpy: ") + hipGetErrorString(e));
+    }
+    return static_cast<T*>(p);
+  }
+};
+
+using TableKey = std::vector<int64_t>;
+
+// Tilings and records first built for one call or plan, which gives them back
+// if it cannot complete them (nobody else having asked for them meanwhile).
+struct Made {
+  std::vector<TableKey> tilings, records;
+};
+
 }  // namespace
 
 struct atlas_mesh_s {
+  struct Order {
+    NodeOrder no;
+    DeviceMem mem;
+  };
+  struct Tiling {
+    DevTiles dt;
+    DeviceMem mem;
+    const Made* maker = nullptr;   // who may still give it back
+  };
+  struct Records {
+    const void* p = nullptr;
+    DevTiles dt;
+    DeviceMem mem;
+    const Made* maker = nullptr;
+  };
+
   HostMesh host;
   int device = -1;
   int num_cus = 0;
-  std::vector<void*> allocations;
+  DeviceMem base;                                      // the operator tables
   DevTables tab64, tab32;
   double* vol = nullptr;
   std::mutex scratch_mu;
@@ -72,34 +135,21 @@ struct atlas_mesh_s {
   size_t scratch_bytes = 0;
   Shape shape[OP_COUNT][3];
   std::mutex order_mu;
-  std::map<std::pair<int, int>, NodeOrder> orders;   // (band rows, run) -> device node order
+  std::map<std::pair<int, int>, Order> orders;         // (band rows, run) -> device node order
   OpTables host_nbr;                                   // neighbour tables only (tile building)
-  std::map<std::vector<int64_t>, DevTiles> tilings;   // tiling key -> device tiles
-  std::map<std::vector<int64_t>, void*> records;      // tiling key + (op, dtype) -> packed node records
+  std::map<TableKey, Tiling> tilings;                  // tiling key -> device tiles
+  std::map<TableKey, Records> records;                 // tiling key + (op, dtype) -> packed node records
+  std::set<TableKey> refused;                          // records that calls with another path do without
 
   ~atlas_mesh_s() {
     if (device >= 0) {
       DeviceGuard g(device);
-      for (void* p : allocations) (void)hipFree(p);
+      records.clear();
+      tilings.clear();
+      orders.clear();
+      base.release();
       if (scratch) (void)hipFree(scratch);
     }
-  }
-
-  template <class T>
-  T* upload(const std::vector<T>& v) {
-    void* p = nullptr;
-    const size_t bytes = v.size() * sizeof(T);
-    hipError_t e = hipMalloc(&p, bytes ? bytes : 16);
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      throw std::bad_alloc();
-    }
-    allocations.push_back(p);
-    if (bytes) {
-      e = hipMemcpy(p, v.data(), bytes, hipMemcpyHostToDevice);
-      if (e != hipSuccess) throw std::runtime_error(std::string("hipMemcpy: ") + hipGetErrorString(e));
-    }
-    return static_cast<T*>(p);
   }
 
   const DevTables& tables(int dtype) const { return dtype == ATLAS_F64 ? tab64 : tab32; }
@@ -109,35 +159,47 @@ struct atlas_mesh_s {
     const std::pair<int, int> key(band_rows_of(sh), run_nodes_of(sh));
     std::lock_guard<std::mutex> lk(order_mu);
     auto it = orders.find(key);
-    if (it != orders.end()) return it->second;
+    if (it != orders.end()) return it->second.no;
     std::vector<int32_t> ord, runs;
     build_band_order(host, key.first, key.second, ord);
     build_band_runs(host, key.first, key.second, runs);
-    NodeOrder no;
-    no.order = upload(ord);
-    no.runs = upload(runs);
-    no.nruns = (int64_t)runs.size() / 2;
-    orders[key] = no;
+    Order o;
+    o.no.order = o.mem.upload(ord);
+    o.no.runs = o.mem.upload(runs);
+    o.no.nruns = (int64_t)runs.size() / 2;
+    const NodeOrder no = o.no;
+    orders.emplace(key, std::move(o));
     return no;
   }
 
   // What a tiling is built from.
-  static std::vector<int64_t> tile_key(const TileGeom& g, const Shape& sh) {
+  static TableKey tile_key(const TileGeom& g, const Shape& sh) {
     const int h = sh.band_rows > 0 ? sh.band_rows : kDefaultTileRows;
     const int sweep = sh.run_nodes > 0 ? sh.run_nodes : kDefaultTileSweep;
     return {g.ring, h, sweep, g.col_bytes, g.row_bytes, g.budget, g.block};
   }
 
+  // What its node records are.
+  static TableKey record_key(const TileGeom& g, const Shape& sh, int op, int dtype) {
+    TableKey key = tile_key(g, sh);
+    key.insert(key.end(), {op, dtype});
+    return key;
+  }
+
   // Device tiles of an LDS-tiled launch, built and uploaded on first use.
-  DevTiles tiles(const TileGeom& g, const Shape& sh) {
-    const std::vector<int64_t> key = tile_key(g, sh);
+  DevTiles tiles(const TileGeom& g, const Shape& sh, Made* made = nullptr) {
+    const TableKey key = tile_key(g, sh);
     const int h = (int)key[1], sweep = (int)key[2];
     std::lock_guard<std::mutex> lk(order_mu);
     auto it = tilings.find(key);
-    if (it != tilings.end()) return it->second;
+    if (it != tilings.end()) {
+      if (it->second.maker != made) it->second.maker = nullptr;
+      return it->second.dt;
+    }
     HaloTiles ht;
     build_halo_tiles(host, host_nbr, g.ring, h, sweep, g.col_bytes, g.row_bytes, g.budget, ht);
-    DevTiles dt;
+    Tiling tl;
+    DevTiles& dt = tl.dt;
     // eight pairs of padding: kernels fetch pairs eight at a time
     ht.segs.resize(ht.segs.size() + 16, 0);
     std::vector<int32_t> nblk;
@@ -150,12 +212,12 @@ struct atlas_mesh_s {
       info[4 * t + 3] |= (ht.info[4 * t + 4] - ht.info[4 * t]) << 16;
     }
     schedule_tiles(host, ht, info, h, sched);
-    dt.info = upload(info);
-    dt.sched = upload(sched);
+    dt.info = tl.mem.upload(info);
+    dt.sched = tl.mem.upload(sched);
     dt.nsched = (int64_t)sched.size() / 4;
-    dt.segs = upload(ht.segs);
-    dt.order = upload(ht.order);
-    dt.loc = upload(ht.loc);
+    dt.segs = tl.mem.upload(ht.segs);
+    dt.order = tl.mem.upload(ht.order);
+    dt.loc = tl.mem.upload(ht.loc);
     dt.ntiles = ht.ntiles;
     dt.col_bytes = g.col_bytes;
     dt.row_bytes = g.row_bytes;
@@ -163,39 +225,77 @@ struct atlas_mesh_s {
     for (int64_t t = 0; t < ht.ntiles; ++t)
       lds = std::max(lds, ht.info[4 * t + 2] * g.col_bytes + ht.info[4 * t + 3] * g.row_bytes);
     dt.lds_bytes = (uint32_t)lds;
-    tilings[key] = dt;
-    return dt;
+    const DevTiles r = dt;
+    if (made) made->tilings.push_back(key);
+    tl.maker = made;
+    tilings.emplace(key, std::move(tl));
+    return r;
   }
 
   // Node records of a tiling for (op, dtype), packed on the device on first
-  // use (one allocation of V records, kept until the mesh is freed).
+  // use (one allocation of V records).
   const void* tile_records(const TileGeom& g, const Shape& sh, const DevTiles& dt, int op, int dtype,
-                           hipStream_t stream) {
-    std::vector<int64_t> key = tile_key(g, sh);
-    key.insert(key.end(), {op, dtype});
+                           hipStream_t stream, Made* made = nullptr) {
+    const TableKey key = record_key(g, sh, op, dtype);
     std::lock_guard<std::mutex> lk(order_mu);
     auto it = records.find(key);
-    if (it != records.end()) return it->second;
-    void* p = nullptr;
-    if (hipMalloc(&p, (size_t)host.V * tile_record_bytes(op, dtype)) != hipSuccess) {
-      (void)hipGetLastError();
-      throw std::bad_alloc();
+    if (it != records.end()) {
+      if (it->second.maker != made) it->second.maker = nullptr;
+      return it->second.p;
     }
-    allocations.push_back(p);
+    Records r;
+    r.dt = dt;
+    void* p = r.mem.alloc((size_t)host.V * tile_record_bytes(op, dtype));
     hipError_t e = pack_tile_records(op, dtype, tables(dtype), dt.order, dt.loc, host.V, p, stream);
     // finished before any stream may read the records
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) throw std::runtime_error(std::string("packing tile records: ") + hipGetErrorString(e));
-    records[key] = p;
+    r.p = p;
+    if (made) made->records.push_back(key);
+    r.maker = made;
+    records.emplace(key, std::move(r));
     return p;
   }
 
-  // Whether a tiling and its node records are there already.
-  bool tiles_ready(const TileGeom& g, const Shape& sh, int op, int dtype) {
-    std::vector<int64_t> key = tile_key(g, sh);
-    key.insert(key.end(), {op, dtype});
+  // The end of what `made` noted: its tables stay, or are given back where
+  // no other call has taken them.
+  void settle(Made& made, bool stay) {
+    if (made.tilings.empty() && made.records.empty()) return;
     std::lock_guard<std::mutex> lk(order_mu);
-    return records.count(key) > 0;
+    auto end = [&](auto& tables, std::vector<TableKey>& keys) {
+      for (const TableKey& k : keys) {
+        auto it = tables.find(k);
+        if (it == tables.end() || it->second.maker != &made) continue;
+        if (stay) it->second.maker = nullptr;
+        else tables.erase(it);
+      }
+      keys.clear();
+    };
+    end(records, made.records);
+    end(tilings, made.tilings);
+  }
+
+  // A tiling and its node records that are there already.
+  bool find_tiles(const TableKey& record, DevTiles& dt, const void*& rec, const Made* made) {
+    std::lock_guard<std::mutex> lk(order_mu);
+    auto it = records.find(record);
+    if (it == records.end()) return false;
+    if (it->second.maker && it->second.maker != made) {
+      it->second.maker = nullptr;
+      tilings.at(TableKey(record.begin(), record.end() - 2)).maker = nullptr;
+    }
+    dt = it->second.dt;
+    rec = it->second.p;
+    return true;
+  }
+  // Records that could not be built, and that their calls go without from then on.
+  bool is_refused(const TableKey& record) {
+    std::lock_guard<std::mutex> lk(order_mu);
+    return refused.count(record) > 0;
+  }
+  void refuse(const TableKey& record) {
+    std::lock_guard<std::mutex> lk(order_mu);
+    refused.insert(record);
   }
 };
 
@@ -210,20 +310,20 @@ std::vector<float> to_f32(const std::vector<double>& v) {
 void upload_tables(atlas_mesh_s& m) {
   OpTables t;
   build_op_tables(m.host, t);
-  const int32_t* nbr8 = m.upload(t.nbr8);
-  const int32_t* lap_nbr = m.upload(t.lap_nbr);
+  const int32_t* nbr8 = m.base.upload(t.nbr8);
+  const int32_t* lap_nbr = m.base.upload(t.lap_nbr);
   m.tab64.nbr8 = m.tab32.nbr8 = nbr8;
   m.tab64.lap_nbr = m.tab32.lap_nbr = lap_nbr;
   m.tab64.lap_stride = m.tab32.lap_stride = t.lap_stride;
   const std::vector<double>* src[OP_COUNT] = {&t.grad, &t.div, &t.gradT, &t.divT, nullptr, &t.curl, &t.curlT};
   for (int o = 0; o < OP_COUNT; ++o) {
     if (!src[o]) continue;
-    m.tab64.coef[o] = m.upload(*src[o]);
-    m.tab32.coef[o] = m.upload(to_f32(*src[o]));
+    m.tab64.coef[o] = m.base.upload(*src[o]);
+    m.tab32.coef[o] = m.base.upload(to_f32(*src[o]));
   }
-  m.tab64.lap_w = m.upload(t.lap_w);
-  m.tab32.lap_w = m.upload(to_f32(t.lap_w));
-  m.vol = m.upload(m.host.vol);
+  m.tab64.lap_w = m.base.upload(t.lap_w);
+  m.tab32.lap_w = m.base.upload(to_f32(t.lap_w));
+  m.vol = m.base.upload(m.host.vol);
   m.host_nbr.nbr8 = std::move(t.nbr8);
   m.host_nbr.lap_nbr = std::move(t.lap_nbr);
   m.host_nbr.lap_stride = t.lap_stride;
@@ -344,31 +444,43 @@ int check_shape(Shape& s, const atlas_tune_t* t) {
 // The tiles and node records of a call on LDS tiles (tg.KL > 0), built on
 // first use.  tg.KL = 0 on return: the call runs without them -- short columns
 // whose tiles cannot be built now (the stream is being captured, where
-// nothing can be allocated, or memory is short), for which the gather needs
-// nothing of its own.
+// nothing can be allocated) or could not be for want of memory, after which
+// the mesh does without those: what was built of them is given back, and no
+// later call tries again.
 int call_tiles(atlas_mesh_t mesh, int op, int dtype, TileGeom& tg, const Shape& sh, DevTiles& dt, const void*& rec,
                hipStream_t stream) {
+  Made made;
+  int rc = ATLAS_OK;
   try {
-    if (sh.short_tiles && !mesh->tiles_ready(tg, sh, op, dtype)) {
-      hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-      if (hipStreamIsCapturing(stream, &st) != hipSuccess) (void)hipGetLastError();
-      if (st != hipStreamCaptureStatusNone) {
+    const TableKey key = atlas_mesh_s::record_key(tg, sh, op, dtype);
+    if (!mesh->find_tiles(key, dt, rec, &made)) {
+      if (sh.short_tiles) {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (!mesh->is_refused(key) && hipStreamIsCapturing(stream, &st) != hipSuccess) (void)hipGetLastError();
+        if (st != hipStreamCaptureStatusNone || mesh->is_refused(key)) {
+          tg.KL = 0;
+          return ATLAS_OK;
+        }
+      }
+      try {
+        dt = mesh->tiles(tg, sh, &made);
+        rec = mesh->tile_records(tg, sh, dt, op, dtype, stream, &made);
+      } catch (const std::bad_alloc&) {
+        if (!sh.short_tiles) throw;
+        mesh->refuse(key);
         tg.KL = 0;
-        return ATLAS_OK;
       }
     }
     // tilings depend on the byte sizes only; the level chunk is the call's
-    dt = mesh->tiles(tg, sh);
     dt.KL = tg.KL;
     dt.nchunks = tg.nchunks;
-    rec = mesh->tile_records(tg, sh, dt, op, dtype, stream);
   } catch (const std::bad_alloc&) {
-    if (!sh.short_tiles) return fail(ATLAS_ENOMEM, "cannot allocate the LDS tiles");
-    tg.KL = 0;
+    rc = fail(ATLAS_ENOMEM, "cannot allocate the LDS tiles");
   } catch (const std::exception& ex) {
-    return fail(ATLAS_EHIP, ex.what());
+    rc = fail(ATLAS_EHIP, ex.what());
   }
-  return ATLAS_OK;
+  mesh->settle(made, rc == ATLAS_OK && tg.KL > 0);
+  return rc;
 }
 
 // build: only build what the call needs on first use (tiles, records, node

@@ -1,0 +1,80 @@
+// Host checks of what the C ABI asks of the device: tables and memory, what
+// runs while a stream is captured, which kernels a call launches.  No kernel
+// runs (fake_device.hpp).
+// Usage: device_calls_check SCENARIO
+#include <cstring>
+#include <functional>
+
+#include "atlas_nabla.h"
+#include "fake_device.hpp"
+
+static int bad = 0;
+#define EXPECT(c)                                                                       \
+  do {                                                                                  \
+    if (!(c)) {                                                                         \
+      ++bad;                                                                            \
+      std::printf("line %d: %s (last error: %s)\n", __LINE__, #c, atlas_last_error());  \
+    }                                                                                   \
+  } while (0)
+
+// fields at made-up device addresses, far apart
+static void* field(int k) { return reinterpret_cast<void*>((uintptr_t(k) + 1) << 44); }
+static hipStream_t stream(int k) { return reinterpret_cast<hipStream_t>(uintptr_t(0x100 + k)); }
+
+struct Mesh {
+  atlas_mesh_t h = nullptr;
+  int64_t V = 0;
+  explicit Mesh(const char* grid) {
+    EXPECT(atlas_mesh_build(grid, 6371220.0, 0, &h) == ATLAS_OK);
+    EXPECT(atlas_mesh_sizes(h, &V, nullptr, nullptr, nullptr, nullptr, nullptr) == ATLAS_OK);
+  }
+  ~Mesh() { atlas_mesh_free(h); }
+};
+
+// Columns of 8 to 32 levels of a field of 2.6 million values take the tiles;
+// where memory is short they run on the gather, and what they could not
+// complete is given back and not tried again.
+static void short_columns_out_of_memory() {
+  Mesh m("O200");
+  const int L = 19;
+  EXPECT(atlas_nabla_gradient(m.h, ATLAS_F32, 3, field(0), field(1), nullptr) == ATLAS_OK);   // the gather's order
+  const size_t held = dev().live;
+  // room for some of the tiling's tables and for all but the records
+  for (size_t room : {size_t(1) << 20, size_t(8) * m.V, size_t(60) * m.V}) {
+    Mesh n("O200");
+    EXPECT(atlas_nabla_gradient(n.h, ATLAS_F32, 3, field(0), field(1), nullptr) == ATLAS_OK);
+    const size_t before = dev().live;
+    dev().limit = before + room;
+    dev().launches.clear();
+    EXPECT(atlas_nabla_gradient(n.h, ATLAS_F32, L, field(0), field(1), nullptr) == ATLAS_OK);
+    EXPECT(dev().refused > 0 && dev().count("k_op<") == 1 && dev().count("k_tile<") == 0);
+    EXPECT(dev().live == before);
+    const int asked = dev().mallocs;
+    for (int i = 0; i < 3; ++i)
+      EXPECT(atlas_nabla_gradient(n.h, ATLAS_F32, L, field(0), field(1), nullptr) == ATLAS_OK);
+    EXPECT(dev().mallocs == asked && dev().live == before && dev().count("k_op<") == 4);
+    dev().limit = SIZE_MAX;
+    dev().refused = 0;
+    // another operator is not held back by it
+    EXPECT(atlas_nabla_divergence(n.h, ATLAS_F32, L, field(0), field(2), nullptr) == ATLAS_OK);
+    EXPECT(dev().count("k_tile<") == 1);
+  }
+  EXPECT(dev().live == held);
+  // long columns: an error, as ever, and nothing kept of the attempt
+  dev().limit = held + 60 * m.V;
+  for (int i = 0; i < 3; ++i)
+    EXPECT(atlas_nabla_gradient(m.h, ATLAS_F32, 60, field(0), field(1), nullptr) == ATLAS_ENOMEM);
+  EXPECT(dev().live == held);
+  dev().limit = SIZE_MAX;
+  EXPECT(atlas_nabla_gradient(m.h, ATLAS_F32, 60, field(0), field(1), nullptr) == ATLAS_OK);
+}
+
+int main(int argc, char** argv) {
+  const std::map<std::string, std::function<void()>> scenarios = {
+      {"short_columns_out_of_memory", short_columns_out_of_memory},
+  };
+  if (argc != 2 || !scenarios.count(argv[1])) return 2;
+  scenarios.at(argv[1])();
+  std::printf(bad ? "FAILED\n" : "OK\n");
+  return bad ? 1 : 0;
+}
