@@ -463,6 +463,9 @@ int call_tiles(atlas_mesh_t mesh, int op, int dtype, TileGeom& tg, const Shape& 
         }
       }
       try {
+        // the gather's order, which short columns of other level counts and
+        // operators may need first while a stream is captured
+        if (sh.short_tiles) (void)mesh->order(Shape());
         dt = mesh->tiles(tg, sh, &made);
         rec = mesh->tile_records(tg, sh, dt, op, dtype, stream, &made);
       } catch (const std::bad_alloc&) {

@@ -69,9 +69,28 @@ static void short_columns_out_of_memory() {
   EXPECT(atlas_nabla_gradient(m.h, ATLAS_F32, 60, field(0), field(1), nullptr) == ATLAS_OK);
 }
 
+// After one call on short columns, whichever path it took, calls of other
+// short columns and operators can be captured: those without tiles of their
+// own record the gather, whose node order is there.
+static void short_columns_captured() {
+  for (int warm : {3, 19}) {
+    Mesh m("O200");
+    EXPECT(atlas_nabla_gradient(m.h, ATLAS_F32, warm, field(0), field(1), nullptr) == ATLAS_OK);
+    dev().launches.clear();
+    dev().here.insert(stream(1));
+    for (int L : {7, 18, 20}) {
+      EXPECT(atlas_nabla_gradient(m.h, ATLAS_F32, L, field(0), field(1), stream(1)) == ATLAS_OK);
+      EXPECT(atlas_nabla_divergence_curl(m.h, ATLAS_F64, L, field(0), field(2), field(3), stream(1)) == ATLAS_OK);
+    }
+    EXPECT(dev().count("k_op<") == 9 && dev().launches.size() == 9 && dev().broken == 0);
+    dev().here.clear();
+  }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> scenarios = {
       {"short_columns_out_of_memory", short_columns_out_of_memory},
+      {"short_columns_captured", short_columns_captured},
   };
   if (argc != 2 || !scenarios.count(argv[1])) return 2;
   scenarios.at(argv[1])();
