@@ -85,15 +85,30 @@ struct DeviceMem {
     blocks.push_back(p);
     return p;
   }
+  // on: copied on that stream and waited for there, else by hipMemcpy.
   template <class T>
-  T* upload(const std::vector<T>& v) {
+  T* upload(const std::vector<T>& v, const hipStream_t* on = nullptr) {
     const size_t bytes = v.size() * sizeof(T);
     void* p = alloc(bytes);
     if (bytes) {
-      const hipError_t e = hipMemcpy(p, v.data(), bytes, hipMemcpyHostToDevice);
+      hipError_t e = on ? hipMemcpyAsync(p, v.data(), bytes, hipMemcpyHostToDevice, *on)
+                        : hipMemcpy(p, v.data(), bytes, hipMemcpyHostToDevice);
+      if (e == hipSuccess && on) e = hipStreamSynchronize(*on);
       if (e != hipSuccess) throw std::runtime_error(std::string("hipMemcpy: ") + hipGetErrorString(e));
     }
     return static_cast<T*>(p);
+  }
+};
+
+// Lets the calling thread allocate while some stream is captured (in the
+// global mode of another thread, or one of its own): for tables whose calls
+// asked for nothing but a launch before the tables were there.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  bool swapped;
+  explicit RelaxedCapture(bool wanted) : swapped(wanted && hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {}
+  ~RelaxedCapture() {
+    if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
   }
 };
 
@@ -155,7 +170,7 @@ struct atlas_mesh_s {
   const DevTables& tables(int dtype) const { return dtype == ATLAS_F64 ? tab64 : tab32; }
 
   // Device node order for a launch shape, built and uploaded on first use.
-  NodeOrder order(const Shape& sh) {
+  NodeOrder order(const Shape& sh, const hipStream_t* on = nullptr) {
     const std::pair<int, int> key(band_rows_of(sh), run_nodes_of(sh));
     std::lock_guard<std::mutex> lk(order_mu);
     auto it = orders.find(key);
@@ -164,8 +179,8 @@ struct atlas_mesh_s {
     build_band_order(host, key.first, key.second, ord);
     build_band_runs(host, key.first, key.second, runs);
     Order o;
-    o.no.order = o.mem.upload(ord);
-    o.no.runs = o.mem.upload(runs);
+    o.no.order = o.mem.upload(ord, on);
+    o.no.runs = o.mem.upload(runs, on);
     o.no.nruns = (int64_t)runs.size() / 2;
     const NodeOrder no = o.no;
     orders.emplace(key, std::move(o));
@@ -187,7 +202,7 @@ struct atlas_mesh_s {
   }
 
   // Device tiles of an LDS-tiled launch, built and uploaded on first use.
-  DevTiles tiles(const TileGeom& g, const Shape& sh, Made* made = nullptr) {
+  DevTiles tiles(const TileGeom& g, const Shape& sh, Made* made = nullptr, const hipStream_t* on = nullptr) {
     const TableKey key = tile_key(g, sh);
     const int h = (int)key[1], sweep = (int)key[2];
     std::lock_guard<std::mutex> lk(order_mu);
@@ -212,12 +227,12 @@ struct atlas_mesh_s {
       info[4 * t + 3] |= (ht.info[4 * t + 4] - ht.info[4 * t]) << 16;
     }
     schedule_tiles(host, ht, info, h, sched);
-    dt.info = tl.mem.upload(info);
-    dt.sched = tl.mem.upload(sched);
+    dt.info = tl.mem.upload(info, on);
+    dt.sched = tl.mem.upload(sched, on);
     dt.nsched = (int64_t)sched.size() / 4;
-    dt.segs = tl.mem.upload(ht.segs);
-    dt.order = tl.mem.upload(ht.order);
-    dt.loc = tl.mem.upload(ht.loc);
+    dt.segs = tl.mem.upload(ht.segs, on);
+    dt.order = tl.mem.upload(ht.order, on);
+    dt.loc = tl.mem.upload(ht.loc, on);
     dt.ntiles = ht.ntiles;
     dt.col_bytes = g.col_bytes;
     dt.row_bytes = g.row_bytes;
@@ -276,11 +291,11 @@ struct atlas_mesh_s {
   }
 
   // A tiling and its node records that are there already.
-  bool find_tiles(const TableKey& record, DevTiles& dt, const void*& rec, const Made* made) {
+  bool find_tiles(const TableKey& record, DevTiles& dt, const void*& rec) {
     std::lock_guard<std::mutex> lk(order_mu);
     auto it = records.find(record);
     if (it == records.end()) return false;
-    if (it->second.maker && it->second.maker != made) {
+    if (it->second.maker) {
       it->second.maker = nullptr;
       tilings.at(TableKey(record.begin(), record.end() - 2)).maker = nullptr;
     }
@@ -441,6 +456,34 @@ int check_shape(Shape& s, const atlas_tune_t* t) {
   return ATLAS_OK;
 }
 
+// Builds the tiles and node records of a call (see call_tiles).
+int build_tiles(atlas_mesh_t mesh, const TableKey& key, int op, int dtype, TileGeom& tg, const Shape& sh, DevTiles& dt,
+                const void*& rec, hipStream_t stream) {
+  const bool optional = sh.short_tiles;
+  const RelaxedCapture relaxed(optional);
+  const hipStream_t* on = optional ? &stream : nullptr;
+  Made made;
+  int rc = ATLAS_OK;
+  try {
+    // the gather's order, which short columns of other level counts and
+    // operators may need first while a stream is captured
+    if (sh.short_tiles) (void)mesh->order(Shape(), on);
+    dt = mesh->tiles(tg, sh, &made, on);
+    rec = mesh->tile_records(tg, sh, dt, op, dtype, stream, &made);
+  } catch (const std::bad_alloc&) {
+    if (optional) {
+      mesh->refuse(key);
+      tg.KL = 0;
+    } else {
+      rc = fail(ATLAS_ENOMEM, "cannot allocate the LDS tiles");
+    }
+  } catch (const std::exception& ex) {
+    rc = fail(ATLAS_EHIP, ex.what());
+  }
+  mesh->settle(made, rc == ATLAS_OK && tg.KL > 0);
+  return rc;
+}
+
 // The tiles and node records of a call on LDS tiles (tg.KL > 0), built on
 // first use.  tg.KL = 0 on return: the call runs without them -- short columns
 // whose tiles cannot be built now (the stream is being captured, where
@@ -449,40 +492,23 @@ int check_shape(Shape& s, const atlas_tune_t* t) {
 // later call tries again.
 int call_tiles(atlas_mesh_t mesh, int op, int dtype, TileGeom& tg, const Shape& sh, DevTiles& dt, const void*& rec,
                hipStream_t stream) {
-  Made made;
   int rc = ATLAS_OK;
   try {
     const TableKey key = atlas_mesh_s::record_key(tg, sh, op, dtype);
-    if (!mesh->find_tiles(key, dt, rec, &made)) {
+    if (!mesh->find_tiles(key, dt, rec)) {
       if (sh.short_tiles) {
         hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
         if (!mesh->is_refused(key) && hipStreamIsCapturing(stream, &st) != hipSuccess) (void)hipGetLastError();
-        if (st != hipStreamCaptureStatusNone || mesh->is_refused(key)) {
-          tg.KL = 0;
-          return ATLAS_OK;
-        }
+        if (st != hipStreamCaptureStatusNone || mesh->is_refused(key)) tg.KL = 0;
       }
-      try {
-        // the gather's order, which short columns of other level counts and
-        // operators may need first while a stream is captured
-        if (sh.short_tiles) (void)mesh->order(Shape());
-        dt = mesh->tiles(tg, sh, &made);
-        rec = mesh->tile_records(tg, sh, dt, op, dtype, stream, &made);
-      } catch (const std::bad_alloc&) {
-        if (!sh.short_tiles) throw;
-        mesh->refuse(key);
-        tg.KL = 0;
-      }
+      if (tg.KL > 0) rc = build_tiles(mesh, key, op, dtype, tg, sh, dt, rec, stream);
     }
     // tilings depend on the byte sizes only; the level chunk is the call's
     dt.KL = tg.KL;
     dt.nchunks = tg.nchunks;
   } catch (const std::bad_alloc&) {
     rc = fail(ATLAS_ENOMEM, "cannot allocate the LDS tiles");
-  } catch (const std::exception& ex) {
-    rc = fail(ATLAS_EHIP, ex.what());
   }
-  mesh->settle(made, rc == ATLAS_OK && tg.KL > 0);
   return rc;
 }
 

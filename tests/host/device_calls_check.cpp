@@ -87,10 +87,31 @@ static void short_columns_captured() {
   }
 }
 
+// First calls of short columns while another thread captures a stream in the
+// global mode, or this thread another stream: nothing they ask for may break
+// that capture, and the tiles are built.
+static void short_columns_beside_a_capture() {
+  for (int whose = 0; whose < 2; ++whose) {
+    Mesh m("O200");
+    EXPECT(atlas_nabla_gradient(m.h, ATLAS_F32, 3, field(0), field(1), nullptr) == ATLAS_OK);
+    dev().launches.clear();
+    if (whose == 0) dev().elsewhere = true;
+    else dev().here.insert(stream(1));
+    for (int L : {18, 20}) {
+      EXPECT(atlas_nabla_gradient(m.h, ATLAS_F32, L, field(0), field(1), stream(2)) == ATLAS_OK);
+      EXPECT(atlas_nabla_gradient(m.h, ATLAS_F32, L, field(0), field(1), nullptr) == ATLAS_OK);
+    }
+    EXPECT(dev().count("k_tile<") == 4 && dev().broken == 0 && dev().mode == hipStreamCaptureModeGlobal);
+    dev().elsewhere = false;
+    dev().here.clear();
+  }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> scenarios = {
       {"short_columns_out_of_memory", short_columns_out_of_memory},
       {"short_columns_captured", short_columns_captured},
+      {"short_columns_beside_a_capture", short_columns_beside_a_capture},
   };
   if (argc != 2 || !scenarios.count(argv[1])) return 2;
   scenarios.at(argv[1])();

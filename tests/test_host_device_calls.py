@@ -24,7 +24,8 @@ def checker():
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["short_columns_out_of_memory", "short_columns_captured"])
+@pytest.mark.parametrize("scenario", ["short_columns_out_of_memory", "short_columns_captured",
+                                      "short_columns_beside_a_capture"])
 def test_device_calls(checker, scenario):
     r = subprocess.run([checker, scenario], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.strip().endswith("OK"), r.stdout + r.stderr
