@@ -62,37 +62,35 @@ size_t dtype_size(int dtype) {
 // Device allocations that are freed together.
 struct DeviceMem {
   std::vector<void*> blocks;
+  size_t bytes = 0;
 
   DeviceMem() = default;
-  DeviceMem(DeviceMem&& o) noexcept : blocks(std::move(o.blocks)) { o.blocks.clear(); }
-  DeviceMem& operator=(DeviceMem&& o) noexcept {
-    std::swap(blocks, o.blocks);
-    return *this;
-  }
+  DeviceMem(DeviceMem&& o) noexcept : blocks(std::move(o.blocks)), bytes(o.bytes) { o.blocks.clear(); }
   ~DeviceMem() { release(); }
 
   void release() {
     for (void* p : blocks) (void)hipFree(p);
     blocks.clear();
   }
-  void* alloc(size_t bytes) {
+  void* alloc(size_t n) {
     blocks.reserve(blocks.size() + 1);
     void* p = nullptr;
-    if (hipMalloc(&p, bytes ? bytes : 16) != hipSuccess) {
+    if (hipMalloc(&p, n ? n : 16) != hipSuccess) {
       (void)hipGetLastError();
       throw std::bad_alloc();
     }
     blocks.push_back(p);
+    bytes += n;
     return p;
   }
   // on: copied on that stream and waited for there, else by hipMemcpy.
   template <class T>
   T* upload(const std::vector<T>& v, const hipStream_t* on = nullptr) {
-    const size_t bytes = v.size() * sizeof(T);
-    void* p = alloc(bytes);
-    if (bytes) {
-      hipError_t e = on ? hipMemcpyAsync(p, v.data(), bytes, hipMemcpyHostToDevice, *on)
-                        : hipMemcpy(p, v.data(), bytes, hipMemcpyHostToDevice);
+    const size_t n = v.size() * sizeof(T);
+    void* p = alloc(n);
+    if (n) {
+      hipError_t e = on ? hipMemcpyAsync(p, v.data(), n, hipMemcpyHostToDevice, *on)
+                        : hipMemcpy(p, v.data(), n, hipMemcpyHostToDevice);
       if (e == hipSuccess && on) e = hipStreamSynchronize(*on);
       if (e != hipSuccess) throw std::runtime_error(std::string("hipMemcpy: ") + hipGetErrorString(e));
     }
@@ -155,6 +153,7 @@ struct atlas_mesh_s {
   std::map<TableKey, Tiling> tilings;                  // tiling key -> device tiles
   std::map<TableKey, Records> records;                 // tiling key + (op, dtype) -> packed node records
   std::set<TableKey> refused;                          // records that calls with another path do without
+  size_t short_bytes = 0, short_limit = 0;             // tables first built for short columns, and their bound
 
   ~atlas_mesh_s() {
     if (device >= 0) {
@@ -273,16 +272,22 @@ struct atlas_mesh_s {
   }
 
   // The end of what `made` noted: its tables stay, or are given back where
-  // no other call has taken them.
-  void settle(Made& made, bool stay) {
+  // no other call has taken them.  Short columns: what stays counts towards
+  // short_limit.
+  void settle(Made& made, bool stay, bool short_columns) {
     if (made.tilings.empty() && made.records.empty()) return;
     std::lock_guard<std::mutex> lk(order_mu);
     auto end = [&](auto& tables, std::vector<TableKey>& keys) {
       for (const TableKey& k : keys) {
         auto it = tables.find(k);
-        if (it == tables.end() || it->second.maker != &made) continue;
-        if (stay) it->second.maker = nullptr;
-        else tables.erase(it);
+        if (it == tables.end()) continue;
+        const bool mine = it->second.maker == &made;
+        if (mine && !stay) {
+          tables.erase(it);
+          continue;
+        }
+        if (mine) it->second.maker = nullptr;
+        if (short_columns) short_bytes += it->second.mem.bytes;
       }
       keys.clear();
     };
@@ -303,10 +308,11 @@ struct atlas_mesh_s {
     rec = it->second.p;
     return true;
   }
-  // Records that could not be built, and that their calls go without from then on.
+  // Records that could not be built, and that their calls go without from then
+  // on: so do further ones of short columns once short_limit is reached.
   bool is_refused(const TableKey& record) {
     std::lock_guard<std::mutex> lk(order_mu);
-    return refused.count(record) > 0;
+    return refused.count(record) > 0 || short_bytes >= short_limit;
   }
   void refuse(const TableKey& record) {
     std::lock_guard<std::mutex> lk(order_mu);
@@ -480,7 +486,7 @@ int build_tiles(atlas_mesh_t mesh, const TableKey& key, int op, int dtype, TileG
   } catch (const std::exception& ex) {
     rc = fail(ATLAS_EHIP, ex.what());
   }
-  mesh->settle(made, rc == ATLAS_OK && tg.KL > 0);
+  mesh->settle(made, rc == ATLAS_OK && tg.KL > 0, sh.short_tiles);
   return rc;
 }
 
@@ -489,7 +495,8 @@ int build_tiles(atlas_mesh_t mesh, const TableKey& key, int op, int dtype, TileG
 // whose tiles cannot be built now (the stream is being captured, where
 // nothing can be allocated) or could not be for want of memory, after which
 // the mesh does without those: what was built of them is given back, and no
-// later call tries again.
+// later call tries again.  Each short level count has tables of its own, which
+// the gather does without, so they are bounded: short_limit a mesh, first come.
 int call_tiles(atlas_mesh_t mesh, int op, int dtype, TileGeom& tg, const Shape& sh, DevTiles& dt, const void*& rec,
                hipStream_t stream) {
   int rc = ATLAS_OK;
@@ -624,9 +631,10 @@ int atlas_mesh_build(const char* grid, double radius, int device, atlas_mesh_t* 
         return fail(ATLAS_EHIP, "cannot select device");
       }
       m->device = device;
-      hipDeviceProp_t prop;
+      hipDeviceProp_t prop{};
       if (hipGetDeviceProperties(&prop, device) == hipSuccess) m->num_cus = prop.multiProcessorCount;
       if (m->num_cus <= 0) m->num_cus = 256;
+      m->short_limit = prop.totalGlobalMem / kShortTableShare;
       upload_tables(*m);
     }
   } catch (const std::bad_alloc&) {

@@ -69,6 +69,10 @@ struct Shape {
 constexpr int kXcdSchedule = 2;
 constexpr int kShortTileLevels = 8;             // fewest levels and values (nodes x levels) of a field of
 constexpr int64_t kShortTileValues = 5 << 19;   // columns of at most 32 levels that takes LDS tiles
+// Part of the device's memory that the tables of short columns may reach on a
+// mesh: 18 GB, two dozen (operator, level count) pairs of FP32 at O1280 (0.77
+// GB each), some hundred at O640.
+constexpr size_t kShortTableShare = 16;
 constexpr int kDefaultBandRows = 32;
 constexpr int kDefaultRunNodes = 16;
 constexpr int kDefaultWindowRunNodes = 64;

@@ -107,11 +107,37 @@ static void short_columns_beside_a_capture() {
   }
 }
 
+// What short columns keep of tables grows with the level counts in use, up to
+// a sixteenth of the device's memory a mesh; further ones run on the gather,
+// the ones that have tables keep them.
+static void short_columns_table_budget() {
+  dev().total = size_t(1) << 30;
+  Mesh m("O200");
+  EXPECT(atlas_nabla_gradient(m.h, ATLAS_F32, 3, field(0), field(1), nullptr) == ATLAS_OK);
+  const size_t held = dev().live;
+  int tiles = 0;
+  for (int pass = 0; pass < 2; ++pass) {
+    dev().launches.clear();
+    for (int L = 16; L <= 32; ++L)
+      EXPECT(atlas_nabla_gradient(m.h, ATLAS_F32, L, field(0), field(1), nullptr) == ATLAS_OK);
+    if (pass == 0) tiles = dev().count("k_tile<");
+    EXPECT(tiles > 1 && tiles < 17 && dev().count("k_tile<") == tiles && dev().count("k_op<") == 17 - tiles);
+    // the table that reaches the bound is the last
+    const size_t kept = dev().live - held, one = kept / tiles;
+    EXPECT(kept >= dev().total / 16 && kept <= dev().total / 16 + 2 * one);
+  }
+  // long columns have no such bound
+  for (int L = 60; L < 64; ++L)
+    EXPECT(atlas_nabla_gradient(m.h, ATLAS_F32, L, field(0), field(1), nullptr) == ATLAS_OK);
+  EXPECT(dev().count("k_win<") == 0);
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> scenarios = {
       {"short_columns_out_of_memory", short_columns_out_of_memory},
       {"short_columns_captured", short_columns_captured},
       {"short_columns_beside_a_capture", short_columns_beside_a_capture},
+      {"short_columns_table_budget", short_columns_table_budget},
   };
   if (argc != 2 || !scenarios.count(argv[1])) return 2;
   scenarios.at(argv[1])();

@@ -16,7 +16,8 @@
 
 struct FakeDevice {
   // memory
-  size_t limit = SIZE_MAX, live = 0;   // bytes the device has, and holds
+  size_t total = size_t(288) << 30;    // bytes the device says it has
+  size_t limit = SIZE_MAX, live = 0;   // bytes it has left to give, and holds
   int mallocs = 0, refused = 0;
   std::map<uintptr_t, size_t> blocks;
   uintptr_t next = uintptr_t(1) << 40;
@@ -111,6 +112,7 @@ hipError_t hipGetDeviceCount(int* n) {
 }
 hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) {
   p->multiProcessorCount = 256;
+  p->totalGlobalMem = dev().total;
   return hipSuccess;
 }
 const char* hipGetErrorString(hipError_t e) {
