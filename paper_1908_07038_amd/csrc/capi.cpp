@@ -114,8 +114,11 @@ using TableKey = std::vector<int64_t>;
 
 // Tilings and records first built for one call or plan, which gives them back
 // if it cannot complete them (nobody else having asked for them meanwhile).
+// parent: the plan that a call builds for, which then has them to give back.
 struct Made {
+  Made* parent = nullptr;
   std::vector<TableKey> tilings, records;
+  bool owns(const Made* maker) const { return maker == this || (parent && maker == parent); }
 };
 
 }  // namespace
@@ -129,12 +132,14 @@ struct atlas_mesh_s {
     DevTiles dt;
     DeviceMem mem;
     const Made* maker = nullptr;   // who may still give it back
+    bool counted = false;          // in short_bytes
   };
   struct Records {
     const void* p = nullptr;
     DevTiles dt;
     DeviceMem mem;
     const Made* maker = nullptr;
+    bool counted = false;
   };
 
   HostMesh host;
@@ -207,7 +212,7 @@ struct atlas_mesh_s {
     std::lock_guard<std::mutex> lk(order_mu);
     auto it = tilings.find(key);
     if (it != tilings.end()) {
-      if (it->second.maker != made) it->second.maker = nullptr;
+      if (!made || !made->owns(it->second.maker)) it->second.maker = nullptr;
       return it->second.dt;
     }
     HaloTiles ht;
@@ -242,6 +247,10 @@ struct atlas_mesh_s {
     const DevTiles r = dt;
     if (made) made->tilings.push_back(key);
     tl.maker = made;
+    if (sh.short_tiles) {
+      tl.counted = true;
+      short_bytes += tl.mem.bytes;
+    }
     tilings.emplace(key, std::move(tl));
     return r;
   }
@@ -254,7 +263,7 @@ struct atlas_mesh_s {
     std::lock_guard<std::mutex> lk(order_mu);
     auto it = records.find(key);
     if (it != records.end()) {
-      if (it->second.maker != made) it->second.maker = nullptr;
+      if (!made || !made->owns(it->second.maker)) it->second.maker = nullptr;
       return it->second.p;
     }
     Records r;
@@ -267,40 +276,43 @@ struct atlas_mesh_s {
     r.p = p;
     if (made) made->records.push_back(key);
     r.maker = made;
+    if (sh.short_tiles) {
+      r.counted = true;
+      short_bytes += r.mem.bytes;
+    }
     records.emplace(key, std::move(r));
     return p;
   }
 
-  // The end of what `made` noted: its tables stay, or are given back where
-  // no other call has taken them.  Short columns: what stays counts towards
-  // short_limit.
-  void settle(Made& made, bool stay, bool short_columns) {
+  // The end of what `made` noted: its tables stay (the parent's to give back,
+  // if there is one), or are given back where no other call has taken them.
+  void settle(Made& made, bool stay) {
     if (made.tilings.empty() && made.records.empty()) return;
     std::lock_guard<std::mutex> lk(order_mu);
-    auto end = [&](auto& tables, std::vector<TableKey>& keys) {
-      for (const TableKey& k : keys) {
+    auto end = [&](auto& tables, std::vector<TableKey>& keys, std::vector<TableKey>* parents) {
+      for (TableKey& k : keys) {
         auto it = tables.find(k);
-        if (it == tables.end()) continue;
-        const bool mine = it->second.maker == &made;
-        if (mine && !stay) {
+        if (it == tables.end() || it->second.maker != &made) continue;
+        if (stay) {
+          it->second.maker = made.parent;
+          if (parents) parents->push_back(std::move(k));   // room there, see build_tiles
+        } else {
+          if (it->second.counted) short_bytes -= it->second.mem.bytes;
           tables.erase(it);
-          continue;
         }
-        if (mine) it->second.maker = nullptr;
-        if (short_columns) short_bytes += it->second.mem.bytes;
       }
       keys.clear();
     };
-    end(records, made.records);
-    end(tilings, made.tilings);
+    end(records, made.records, made.parent ? &made.parent->records : nullptr);
+    end(tilings, made.tilings, made.parent ? &made.parent->tilings : nullptr);
   }
 
   // A tiling and its node records that are there already.
-  bool find_tiles(const TableKey& record, DevTiles& dt, const void*& rec) {
+  bool find_tiles(const TableKey& record, DevTiles& dt, const void*& rec, const Made* made) {
     std::lock_guard<std::mutex> lk(order_mu);
     auto it = records.find(record);
     if (it == records.end()) return false;
-    if (it->second.maker) {
+    if (it->second.maker && it->second.maker != made) {
       it->second.maker = nullptr;
       tilings.at(TableKey(record.begin(), record.end() - 2)).maker = nullptr;
     }
@@ -312,7 +324,8 @@ struct atlas_mesh_s {
   // on: so do further ones of short columns once short_limit is reached.
   bool is_refused(const TableKey& record) {
     std::lock_guard<std::mutex> lk(order_mu);
-    return refused.count(record) > 0 || short_bytes >= short_limit;
+    if (short_bytes >= short_limit) refused.insert(record);
+    return refused.count(record) > 0;
   }
   void refuse(const TableKey& record) {
     std::lock_guard<std::mutex> lk(order_mu);
@@ -464,13 +477,19 @@ int check_shape(Shape& s, const atlas_tune_t* t) {
 
 // Builds the tiles and node records of a call (see call_tiles).
 int build_tiles(atlas_mesh_t mesh, const TableKey& key, int op, int dtype, TileGeom& tg, const Shape& sh, DevTiles& dt,
-                const void*& rec, hipStream_t stream) {
+                const void*& rec, hipStream_t stream, Made* build) {
   const bool optional = sh.short_tiles;
   const RelaxedCapture relaxed(optional);
   const hipStream_t* on = optional ? &stream : nullptr;
   Made made;
+  made.parent = build;
   int rc = ATLAS_OK;
+  bool refused = false;
   try {
+    if (build) {
+      build->tilings.reserve(build->tilings.size() + 1);
+      build->records.reserve(build->records.size() + 1);
+    }
     // the gather's order, which short columns of other level counts and
     // operators may need first while a stream is captured
     if (sh.short_tiles) (void)mesh->order(Shape(), on);
@@ -478,7 +497,7 @@ int build_tiles(atlas_mesh_t mesh, const TableKey& key, int op, int dtype, TileG
     rec = mesh->tile_records(tg, sh, dt, op, dtype, stream, &made);
   } catch (const std::bad_alloc&) {
     if (optional) {
-      mesh->refuse(key);
+      refused = true;
       tg.KL = 0;
     } else {
       rc = fail(ATLAS_ENOMEM, "cannot allocate the LDS tiles");
@@ -486,7 +505,8 @@ int build_tiles(atlas_mesh_t mesh, const TableKey& key, int op, int dtype, TileG
   } catch (const std::exception& ex) {
     rc = fail(ATLAS_EHIP, ex.what());
   }
-  mesh->settle(made, rc == ATLAS_OK && tg.KL > 0, sh.short_tiles);
+  mesh->settle(made, rc == ATLAS_OK && tg.KL > 0);
+  if (refused) mesh->refuse(key);
   return rc;
 }
 
@@ -498,17 +518,17 @@ int build_tiles(atlas_mesh_t mesh, const TableKey& key, int op, int dtype, TileG
 // later call tries again.  Each short level count has tables of its own, which
 // the gather does without, so they are bounded: short_limit a mesh, first come.
 int call_tiles(atlas_mesh_t mesh, int op, int dtype, TileGeom& tg, const Shape& sh, DevTiles& dt, const void*& rec,
-               hipStream_t stream) {
+               hipStream_t stream, Made* build) {
   int rc = ATLAS_OK;
   try {
     const TableKey key = atlas_mesh_s::record_key(tg, sh, op, dtype);
-    if (!mesh->find_tiles(key, dt, rec)) {
+    if (!mesh->find_tiles(key, dt, rec, build)) {
       if (sh.short_tiles) {
         hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
         if (!mesh->is_refused(key) && hipStreamIsCapturing(stream, &st) != hipSuccess) (void)hipGetLastError();
         if (st != hipStreamCaptureStatusNone || mesh->is_refused(key)) tg.KL = 0;
       }
-      if (tg.KL > 0) rc = build_tiles(mesh, key, op, dtype, tg, sh, dt, rec, stream);
+      if (tg.KL > 0) rc = build_tiles(mesh, key, op, dtype, tg, sh, dt, rec, stream, build);
     }
     // tilings depend on the byte sizes only; the level chunk is the call's
     dt.KL = tg.KL;
@@ -519,11 +539,11 @@ int call_tiles(atlas_mesh_t mesh, int op, int dtype, TileGeom& tg, const Shape& 
   return rc;
 }
 
-// build: only build what the call needs on first use (tiles, records, node
-// order); nothing is launched.  add (OP_DIVT): a field of the output's form
+// build: only build what the call needs on first use (tiles and records, noted
+// there, and the node order); nothing is launched.  add (OP_DIVT): a field of the output's form
 // that the result is added to.
 int run_op(atlas_mesh_t mesh, int op, int dtype, int32_t nlev, const void* in, void* out, void* stream,
-           const Shape* shape_override = nullptr, bool build = false, const void* add = nullptr) {
+           const Shape* shape_override = nullptr, Made* build = nullptr, const void* add = nullptr) {
   int rc = check_mesh_device(mesh);
   if (rc) return rc;
   const size_t es = dtype_size(dtype);
@@ -550,7 +570,7 @@ int run_op(atlas_mesh_t mesh, int op, int dtype, int32_t nlev, const void* in, v
   DevTiles dt;
   const void* rec = nullptr;
   // tiles asked for and a tile geometry fits the budget
-  if (tg.KL > 0 && (rc = call_tiles(mesh, op, dtype, tg, sh, dt, rec, (hipStream_t)stream))) return rc;
+  if (tg.KL > 0 && (rc = call_tiles(mesh, op, dtype, tg, sh, dt, rec, (hipStream_t)stream, build))) return rc;
   if (tg.KL > 0) {
     if (build) return ATLAS_OK;
     const bool fused = add && sh.lds_tiles == 3;
@@ -728,7 +748,7 @@ int atlas_nabla_divergence_adjoint(atlas_mesh_t mesh, int dtype, int32_t nlev, c
 int atlas_nabla_divergence_adjoint_add(atlas_mesh_t mesh, int dtype, int32_t nlev, const void* d, const void* base,
                                        void* uvbar, void* stream) {
   if (!base) return fail(ATLAS_EINVAL, "base is NULL");
-  return run_op(mesh, OP_DIVT, dtype, nlev, d, uvbar, stream, nullptr, false, base);
+  return run_op(mesh, OP_DIVT, dtype, nlev, d, uvbar, stream, nullptr, nullptr, base);
 }
 
 int atlas_nabla_curl(atlas_mesh_t mesh, int dtype, int32_t nlev, const void* uv, void* zeta, void* stream) {
@@ -781,7 +801,7 @@ int atlas_nabla_gradient_laplacian(atlas_mesh_t mesh, int dtype, int32_t nlev, c
   if (dtype == ATLAS_BF16 && ((uintptr_t)f & 3u)) tg.KL = 0;
   DevTiles dt;
   const void* rec = nullptr;
-  if (tg.KL > 0 && (rc = call_tiles(mesh, OP_GRADLAP, dtype, tg, sh, dt, rec, (hipStream_t)stream))) return rc;
+  if (tg.KL > 0 && (rc = call_tiles(mesh, OP_GRADLAP, dtype, tg, sh, dt, rec, (hipStream_t)stream, nullptr))) return rc;
   if (tg.KL > 0) {
     hipError_t e = launch_tiles(OP_GRADLAP, dtype, dt, rec, nlev, f, lap, sh, mesh->num_cus, (hipStream_t)stream, grad);
     if (e != hipSuccess) return hip_fail(e, "gradient_laplacian");
@@ -800,7 +820,7 @@ namespace {
 // as run_op's).
 int divergence_pair(atlas_mesh_t mesh, int fused, int op2, const char* name, int dtype, int32_t nlev,
                     const void* uv, void* div, void* out2, void* stream, const Shape* shape_override = nullptr,
-                    bool build = false) {
+                    Made* build = nullptr) {
   int rc = check_mesh_device(mesh);
   if (rc) return rc;
   const size_t es = dtype_size(dtype);
@@ -824,7 +844,7 @@ int divergence_pair(atlas_mesh_t mesh, int fused, int op2, const char* name, int
   if (dtype == ATLAS_BF16 && ((uintptr_t)uv & 3u)) tg.KL = 0;
   DevTiles dt;
   const void* rec = nullptr;
-  if (tg.KL > 0 && (rc = call_tiles(mesh, fused, dtype, tg, sh, dt, rec, (hipStream_t)stream))) return rc;
+  if (tg.KL > 0 && (rc = call_tiles(mesh, fused, dtype, tg, sh, dt, rec, (hipStream_t)stream, build))) return rc;
   if (tg.KL > 0) {
     if (build) return ATLAS_OK;
     hipError_t e = launch_tiles(fused, dtype, dt, rec, nlev, uv, div, sh, mesh->num_cus, (hipStream_t)stream, out2);
@@ -1483,7 +1503,7 @@ bool plan_pairs(const atlas_batch_s* b) {
 // One operator over every tracer in field launches, on the mesh's shapes or,
 // where the field form is the library's choice, the default ones; pair: the
 // divergence with the gradient adjoint; build: see run_op.
-int plan_run_fields(atlas_batch_s* b, int o, bool pair, hipStream_t st, bool build = false) {
+int plan_run_fields(atlas_batch_s* b, int o, bool pair, hipStream_t st, Made* build = nullptr) {
   const Shape def;
   const Shape* sh = b->fields ? &def : nullptr;
   for (const atlas_tracer_desc_t& d : b->descs) {
@@ -1503,12 +1523,17 @@ int plan_upload(atlas_batch_s* b) {
   b->pairs = plan_pairs(b);
   b->fields = plan_fields(b);
   if (b->fields) {
-    for (int o = 0; o < 4; ++o) {
+    Made made;
+    int rc = ATLAS_OK;
+    for (int o = 0; o < 4 && !rc; ++o) {
       if (!(b->mask & (1u << o)) || (b->pairs && o == OP_GRADT)) continue;
-      int rc = plan_run_fields(b, o, b->pairs && o == OP_DIV, nullptr, true);
-      if (rc) return rc;
+      rc = plan_run_fields(b, o, b->pairs && o == OP_DIV, nullptr, &made);
     }
-    return ATLAS_OK;
+    b->mesh->settle(made, rc == ATLAS_OK);
+    if (rc != ATLAS_ENOMEM) return rc;
+    // every level count has tables of its own there: the persistent form,
+    // whose tracers of similar depth share them, may still fit
+    b->fields = false;
   }
   for (int o = 0; o < 4; ++o) {
     if (!(b->mask & (1u << o)) || !plan_persistent(b->shape[o])) continue;

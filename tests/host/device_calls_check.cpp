@@ -132,12 +132,75 @@ static void short_columns_table_budget() {
   EXPECT(dev().count("k_win<") == 0);
 }
 
+struct Plan {
+  atlas_batch_t h = nullptr;
+  int rc = 0;
+  Plan(const Mesh& m, std::vector<int> levels, const atlas_tune_t* tune = nullptr, int dtype = ATLAS_F32,
+       uint32_t ops = 0xF) {
+    std::vector<atlas_tracer_desc_t> d(levels.size());
+    for (size_t t = 0; t < d.size(); ++t) {
+      d[t].nlev = levels[t];
+      // field, wind, and an output of each operator
+      d[t].in[0] = d[t].in[3] = field(10 * (int)t);
+      d[t].in[1] = d[t].in[2] = field(10 * (int)t + 1);
+      for (int o = 0; o < 4; ++o) d[t].out[o] = field(10 * (int)t + 2 + o);
+    }
+    rc = atlas_batch_create(m.h, dtype, d.data(), (int)d.size(), ops, tune, &h);
+  }
+  ~Plan() { atlas_batch_free(h); }
+};
+
+// A plan of large fields whose field launches' tables (one set a level count)
+// do not fit takes the persistent form, whose tracers share tilings; what was
+// built for the other is given back.
+static void plan_out_of_memory() {
+  const std::vector<int> levels = {130, 132, 133, 134, 135, 136, 137};
+  size_t fields, shared;
+  {
+    Mesh m("O200");
+    const size_t held = dev().live;
+    Plan p(m, levels);
+    EXPECT(p.rc == ATLAS_OK && atlas_batch_run(p.h, nullptr) == ATLAS_OK);
+    EXPECT(dev().count("k_tile<") == 3 * 7 && dev().count("k_tile_batched<") == 0);
+    fields = dev().live - held;
+  }
+  {
+    Mesh m("O200");
+    const size_t held = dev().live;
+    atlas_tune_t t{};
+    t.batch_mode = 1;
+    Plan p(m, levels, &t);
+    EXPECT(p.rc == ATLAS_OK);
+    shared = dev().live - held;
+  }
+  EXPECT(shared < fields / 2);
+  Mesh m("O200");
+  const size_t held = dev().live;
+  dev().limit = held + shared + shared / 4;
+  {
+    dev().launches.clear();
+    Plan p(m, levels);
+    EXPECT(p.rc == ATLAS_OK && dev().refused > 0);
+    EXPECT(dev().live - held == shared);
+    const int asked = dev().mallocs;
+    EXPECT(atlas_batch_run(p.h, nullptr) == ATLAS_OK);
+    EXPECT(dev().count("k_tile_batched<") == 3 && dev().count("k_tile<") == 0 && dev().mallocs == asked);
+  }
+  // neither fits
+  dev().limit = SIZE_MAX;
+  Mesh n("O200");
+  dev().limit = dev().live + shared / 2;
+  Plan p(n, levels);
+  EXPECT(p.rc == ATLAS_ENOMEM);
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> scenarios = {
       {"short_columns_out_of_memory", short_columns_out_of_memory},
       {"short_columns_captured", short_columns_captured},
       {"short_columns_beside_a_capture", short_columns_beside_a_capture},
       {"short_columns_table_budget", short_columns_table_budget},
+      {"plan_out_of_memory", plan_out_of_memory},
   };
   if (argc != 2 || !scenarios.count(argv[1])) return 2;
   scenarios.at(argv[1])();
