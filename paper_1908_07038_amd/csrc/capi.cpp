@@ -322,9 +322,9 @@ struct atlas_mesh_s {
   }
   // Records that could not be built, and that their calls go without from then
   // on: so do further ones of short columns once short_limit is reached.
-  bool is_refused(const TableKey& record) {
+  bool is_refused(const TableKey& record, bool short_columns) {
     std::lock_guard<std::mutex> lk(order_mu);
-    if (short_bytes >= short_limit) refused.insert(record);
+    if (short_columns && short_bytes >= short_limit) refused.insert(record);
     return refused.count(record) > 0;
   }
   void refuse(const TableKey& record) {
@@ -477,8 +477,7 @@ int check_shape(Shape& s, const atlas_tune_t* t) {
 
 // Builds the tiles and node records of a call (see call_tiles).
 int build_tiles(atlas_mesh_t mesh, const TableKey& key, int op, int dtype, TileGeom& tg, const Shape& sh, DevTiles& dt,
-                const void*& rec, hipStream_t stream, Made* build) {
-  const bool optional = sh.short_tiles;
+                const void*& rec, hipStream_t stream, Made* build, bool optional) {
   const RelaxedCapture relaxed(optional);
   const hipStream_t* on = optional ? &stream : nullptr;
   Made made;
@@ -511,24 +510,26 @@ int build_tiles(atlas_mesh_t mesh, const TableKey& key, int op, int dtype, TileG
 }
 
 // The tiles and node records of a call on LDS tiles (tg.KL > 0), built on
-// first use.  tg.KL = 0 on return: the call runs without them -- short columns
-// whose tiles cannot be built now (the stream is being captured, where
+// first use.  tg.KL = 0 on return: the call runs without them -- short columns,
+// and those that the caller has another way for (or_else), whose tiles cannot be built now (the stream is being captured, where
 // nothing can be allocated) or could not be for want of memory, after which
 // the mesh does without those: what was built of them is given back, and no
 // later call tries again.  Each short level count has tables of its own, which
 // the gather does without, so they are bounded: short_limit a mesh, first come.
 int call_tiles(atlas_mesh_t mesh, int op, int dtype, TileGeom& tg, const Shape& sh, DevTiles& dt, const void*& rec,
-               hipStream_t stream, Made* build) {
+               hipStream_t stream, Made* build, bool or_else = false) {
+  const bool optional = or_else || sh.short_tiles;
   int rc = ATLAS_OK;
   try {
     const TableKey key = atlas_mesh_s::record_key(tg, sh, op, dtype);
     if (!mesh->find_tiles(key, dt, rec, build)) {
-      if (sh.short_tiles) {
+      if (optional) {
         hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-        if (!mesh->is_refused(key) && hipStreamIsCapturing(stream, &st) != hipSuccess) (void)hipGetLastError();
-        if (st != hipStreamCaptureStatusNone || mesh->is_refused(key)) tg.KL = 0;
+        const bool refused = mesh->is_refused(key, sh.short_tiles);
+        if (!refused && hipStreamIsCapturing(stream, &st) != hipSuccess) (void)hipGetLastError();
+        if (refused || st != hipStreamCaptureStatusNone) tg.KL = 0;
       }
-      if (tg.KL > 0) rc = build_tiles(mesh, key, op, dtype, tg, sh, dt, rec, stream, build);
+      if (tg.KL > 0) rc = build_tiles(mesh, key, op, dtype, tg, sh, dt, rec, stream, build, optional);
     }
     // tilings depend on the byte sizes only; the level chunk is the call's
     dt.KL = tg.KL;
@@ -817,10 +818,11 @@ namespace {
 // OP_GRADT) of one vector field: one pass of the dual kernel (fused op
 // OP_DIVCURL or OP_DIVGRADT) on the divergence's launch shape when that is
 // the one-tile LDS form, else the two operators one after the other (build:
-// as run_op's).
+// as run_op's; or_two: the two also where the pair's tables are not there and
+// cannot be built).
 int divergence_pair(atlas_mesh_t mesh, int fused, int op2, const char* name, int dtype, int32_t nlev,
                     const void* uv, void* div, void* out2, void* stream, const Shape* shape_override = nullptr,
-                    Made* build = nullptr) {
+                    Made* build = nullptr, bool or_two = false) {
   int rc = check_mesh_device(mesh);
   if (rc) return rc;
   const size_t es = dtype_size(dtype);
@@ -844,7 +846,7 @@ int divergence_pair(atlas_mesh_t mesh, int fused, int op2, const char* name, int
   if (dtype == ATLAS_BF16 && ((uintptr_t)uv & 3u)) tg.KL = 0;
   DevTiles dt;
   const void* rec = nullptr;
-  if (tg.KL > 0 && (rc = call_tiles(mesh, fused, dtype, tg, sh, dt, rec, (hipStream_t)stream, build))) return rc;
+  if (tg.KL > 0 && (rc = call_tiles(mesh, fused, dtype, tg, sh, dt, rec, (hipStream_t)stream, build, or_two))) return rc;
   if (tg.KL > 0) {
     if (build) return ATLAS_OK;
     hipError_t e = launch_tiles(fused, dtype, dt, rec, nlev, uv, div, sh, mesh->num_cus, (hipStream_t)stream, out2);
@@ -1502,13 +1504,15 @@ bool plan_pairs(const atlas_batch_s* b) {
 
 // One operator over every tracer in field launches, on the mesh's shapes or,
 // where the field form is the library's choice, the default ones; pair: the
-// divergence with the gradient adjoint; build: see run_op.
+// divergence with the gradient adjoint (as two calls where a plan of the
+// former kind, whose tables come with its runs and tuning, is captured or runs
+// out of memory without the pair's); build: see run_op.
 int plan_run_fields(atlas_batch_s* b, int o, bool pair, hipStream_t st, Made* build = nullptr) {
   const Shape def;
   const Shape* sh = b->fields ? &def : nullptr;
   for (const atlas_tracer_desc_t& d : b->descs) {
     int rc = pair ? divergence_pair(b->mesh, OP_DIVGRADT, OP_GRADT, "divergence_gradient_adjoint", b->dtype, d.nlev,
-                                    d.in[OP_DIV], d.out[OP_DIV], d.out[OP_GRADT], st, sh, build)
+                                    d.in[OP_DIV], d.out[OP_DIV], d.out[OP_GRADT], st, sh, build, !b->fields)
                   : run_op(b->mesh, o, b->dtype, d.nlev, d.in[o], d.out[o], st, sh, build);
     if (rc) return rc;
   }

@@ -194,6 +194,33 @@ static void plan_out_of_memory() {
   EXPECT(p.rc == ATLAS_ENOMEM);
 }
 
+// A plan in the field form by request, whose operators' tables are there from
+// single calls (or from tuning) but not the divergence pair's: captured, and
+// short of memory, it runs the two operators; else the pair.
+static void field_plan_pair() {
+  for (int captured = 0; captured < 2; ++captured) {
+    Mesh m("O33");
+    EXPECT(atlas_nabla_divergence(m.h, ATLAS_F32, 60, field(1), field(0), nullptr) == ATLAS_OK);
+    EXPECT(atlas_nabla_gradient_adjoint(m.h, ATLAS_F32, 60, field(1), field(0), nullptr) == ATLAS_OK);
+    atlas_tune_t t{};
+    t.batch_mode = 2;
+    Plan p(m, {60, 60}, &t, ATLAS_F32, ATLAS_OP_DIVERGENCE | ATLAS_OP_GRADIENT_ADJOINT);
+    EXPECT(p.rc == ATLAS_OK);
+    const size_t held = dev().live;
+    dev().launches.clear();
+    if (captured) dev().here.insert(stream(1));
+    else dev().limit = held;
+    EXPECT(atlas_batch_run(p.h, stream(1)) == ATLAS_OK);
+    EXPECT(dev().count("k_tile<float, 1,") == 2 && dev().count("k_tile<float, 2,") == 2 && dev().launches.size() == 4);
+    EXPECT(dev().broken == 0 && dev().live == held);
+    dev().here.clear();
+    dev().limit = SIZE_MAX;
+    dev().launches.clear();
+    EXPECT(atlas_batch_run(p.h, stream(1)) == ATLAS_OK);
+    EXPECT(dev().count("k_tile<float, 8,") == (captured ? 2 : 0));
+  }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> scenarios = {
       {"short_columns_out_of_memory", short_columns_out_of_memory},
@@ -201,6 +228,7 @@ int main(int argc, char** argv) {
       {"short_columns_beside_a_capture", short_columns_beside_a_capture},
       {"short_columns_table_budget", short_columns_table_budget},
       {"plan_out_of_memory", plan_out_of_memory},
+      {"field_plan_pair", field_plan_pair},
   };
   if (argc != 2 || !scenarios.count(argv[1])) return 2;
   scenarios.at(argv[1])();
