@@ -482,7 +482,9 @@ enum {
 
 /* Describe the launch a single-field call of (op, dtype) on nlev levels
  * would make with the mesh's current shape: the shape after per-operator
- * defaults are applied (to *resolved, if not NULL) and the name of the
+ * defaults are applied (to *resolved, if not NULL; for columns of at most 32
+ * levels that the library itself puts on LDS tiles the shape as it is set,
+ * which is what takes them there) and the name of the
  * kernel it runs, e.g. "k_tile<float, 0, 3>" (to kernel, NUL-terminated and
  * truncated to len bytes, if not NULL).  op: one ATLAS_OP_* bit, or one of
  * the one-pass codes above, whose kernel name reads "two calls" when the

@@ -1135,7 +1135,9 @@ int atlas_nabla_describe(atlas_mesh_t mesh, int dtype, uint32_t op, int32_t nlev
   if (kernel && len <= 0) return fail(ATLAS_EINVAL, "len must be positive");
   const int k = fused >= 0 ? fused : o;
   const Shape sh = resolve_shape(k, dtype, nlev, mesh->host.V, mesh->shape[o][dtype]);
-  if (resolved) shape_out(sh, resolved);
+  // short columns on tiles: by the shape as it is set, since none that names
+  // the tiles' parameters takes them there
+  if (resolved) shape_out(sh.short_tiles ? mesh->shape[o][dtype] : sh, resolved);
   if (kernel) {
     // the one-pass calls run their kernel on the one-tile form only
     if (fused >= 0 && !(sh.lds_tiles == 3 && uses_tiles(k, dtype, nlev, sh) && tile_geom(k, dtype, nlev, sh).KL > 0))

@@ -2741,11 +2741,17 @@ hipError_t launch_u(const Args& a, int U, dim3 g, dim3 b, int64_t nblocks, int r
   return hipGetLastError();
 }
 
+// Whether chunks of KL levels run in the short columns' body (U = 0).
+template <class S, int OP>
+constexpr bool short_body(int KL) {
+  return kUseBlk<S, OP, 1> && KL <= 32;
+}
+
 template <class S, int OP>
 hipError_t launch_tile_u(const TileArgs& a, int U, dim3 g, dim3 b, uint32_t lds, int64_t nblocks, int remap,
                          hipStream_t st) {
   if constexpr (kUseBlk<S, OP, 1>) {
-    if (a.KL <= 32) {
+    if (short_body<S, OP>(a.KL)) {
       const void* fn = reinterpret_cast<const void*>(&k_tile<S, OP, 0>);
       if ((int)b.x > kTileThreads<S, OP, 0>) b.x = kTileThreads<S, OP, 0>;
       if (lds > 65536) {
@@ -3350,7 +3356,10 @@ void kernel_label(int op, int dtype, int nlev, const Shape& sh, char* buf, int l
     const TileGeom g = tile_geom(op, dtype, nlev, sh);
     if (g.KL > 0) {
       if (sh.lds_tiles == 3) {
-        U = tile_slices(g.KL, sh);
+        const bool is_short = with_block_op(op, dtype, [&](auto tag, auto k) -> int {
+          return short_body<decltype(tag), decltype(k)::value>(g.KL);
+        });
+        U = is_short ? 0 : tile_slices(g.KL, sh);
       } else {
         const int P = lanes_per_node(g.KL, sh);
         const int nsl = (g.KL + P - 1) / P;

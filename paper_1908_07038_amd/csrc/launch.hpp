@@ -130,7 +130,8 @@ struct TileGeom {
 Shape resolve_shape(int op, int dtype, int nlev, int64_t V, const Shape& sh);
 bool uses_tiles(int op, int dtype, int nlev, const Shape& sh);
 // Name of the kernel template instance a single-field launch with the
-// resolved shape runs, e.g. "k_tile<float, 0, 3>".
+// resolved shape runs, e.g. "k_tile<float, 0, 3>" (the last number the slices
+// a step, 0 for chunks of at most 32 levels in a body of their own).
 void kernel_label(int op, int dtype, int nlev, const Shape& resolved, char* buf, int len);
 TileGeom tile_geom(int op, int dtype, int nlev, const Shape& sh);
 // Bytes of one node record of the tile path (LDS bytes per tile node).

@@ -221,6 +221,58 @@ static void field_plan_pair() {
   }
 }
 
+// atlas_nabla_describe names the kernel that a call launches, and the shape it
+// reports, set on the mesh, keeps that kernel.
+static void described_kernels() {
+  struct Call {
+    uint32_t code, bit;
+    std::function<int(atlas_mesh_t, int, int)> run;
+  };
+  const auto one = [](int (*fn)(atlas_mesh_t, int, int32_t, const void*, void*, void*)) {
+    return [fn](atlas_mesh_t m, int dt, int L) { return fn(m, dt, L, field(0), field(1), nullptr); };
+  };
+  const auto two = [](int (*fn)(atlas_mesh_t, int, int32_t, const void*, void*, void*, void*)) {
+    return [fn](atlas_mesh_t m, int dt, int L) { return fn(m, dt, L, field(0), field(1), field(2), nullptr); };
+  };
+  const std::vector<Call> calls = {
+      {ATLAS_OP_GRADIENT, ATLAS_OP_GRADIENT, one(atlas_nabla_gradient)},
+      {ATLAS_OP_DIVERGENCE, ATLAS_OP_DIVERGENCE, one(atlas_nabla_divergence)},
+      {ATLAS_OP_CURL_ADJOINT, ATLAS_OP_CURL_ADJOINT, one(atlas_nabla_curl_adjoint)},
+      {ATLAS_OP_LAPLACIAN, ATLAS_OP_LAPLACIAN,
+       [](atlas_mesh_t m, int dt, int L) { return atlas_nabla_laplacian(m, dt, L, field(0), field(1), nullptr, nullptr); }},
+      {ATLAS_OP_GRADIENT_LAPLACIAN, ATLAS_OP_LAPLACIAN, two(atlas_nabla_gradient_laplacian)},
+      {ATLAS_OP_DIVERGENCE_CURL, ATLAS_OP_DIVERGENCE, two(atlas_nabla_divergence_curl)},
+      {ATLAS_OP_DIVERGENCE_GRADIENT_ADJOINT, ATLAS_OP_DIVERGENCE, two(atlas_nabla_divergence_gradient_adjoint)},
+  };
+  Mesh m("O200");
+  const auto launched = [&](const Call& c, int dt, int L) {
+    EXPECT(c.run(m.h, dt, L) == ATLAS_OK);   // tables
+    dev().launches.clear();
+    EXPECT(c.run(m.h, dt, L) == ATLAS_OK);
+    return dev().launches.size() == 1 ? dev().launches[0] : std::string("two calls");
+  };
+  for (int dt : {ATLAS_F64, ATLAS_F32, ATLAS_BF16})
+    for (int L : {7, 16, 32, 33, 96, 137, 180})
+      for (const Call& c : calls) {
+        char name[128];
+        atlas_tune_t t{};
+        EXPECT(atlas_nabla_describe(m.h, dt, c.code, L, &t, name, sizeof name) == ATLAS_OK);
+        const std::string run = launched(c, dt, L);
+        if (run != name) {
+          ++bad;
+          std::printf("op %x dtype %d x %d: %s described, %s launched\n", c.code, dt, L, name, run.c_str());
+        }
+        EXPECT(atlas_nabla_set_tune(m.h, dt, c.bit, &t) == ATLAS_OK);
+        const std::string again = launched(c, dt, L);
+        if (again != run) {
+          ++bad;
+          std::printf("op %x dtype %d x %d: %s, with the described shape set %s\n", c.code, dt, L, run.c_str(),
+                      again.c_str());
+        }
+        EXPECT(atlas_nabla_set_tune(m.h, dt, c.bit, nullptr) == ATLAS_OK);
+      }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> scenarios = {
       {"short_columns_out_of_memory", short_columns_out_of_memory},
@@ -229,6 +281,7 @@ int main(int argc, char** argv) {
       {"short_columns_table_budget", short_columns_table_budget},
       {"plan_out_of_memory", plan_out_of_memory},
       {"field_plan_pair", field_plan_pair},
+      {"described_kernels", described_kernels},
   };
   if (argc != 2 || !scenarios.count(argv[1])) return 2;
   scenarios.at(argv[1])();
