@@ -348,8 +348,9 @@ typedef struct {
                                32); LDS tiles: rows per tile (default 4)      */
   int32_t run_nodes;        /* consecutive nodes of a row per run (default 16,
                                64 on the row-window walk); LDS tiles: bands
-                               swept together by longitude (default 8; the
-                               library's own tile shapes mostly take 1)       */
+                               swept together by longitude (default 8, but
+                               for one-tile workgroups in the library's own
+                               order mostly 1)                                */
   int32_t nt_stores;        /* 1: non-temporal output stores, 2: plain (the
                                default)                                      */
   int32_t row_window;       /* 1-ring operators on columns of more than 32

@@ -1237,13 +1237,15 @@ int atlas_nabla_tune(atlas_mesh_t mesh, int dtype, uint32_t op, int32_t nlev, co
   }
   if (bs.lds_tiles == 1 || bs.lds_tiles == 3 ||
       (bs.lds_tiles == 0 && uses_tiles(o, dtype, nlev, resolve_shape(o, dtype, nlev, mesh->host.V, bs)))) {
-    // LDS tiles won: bands swept together (short columns: the default's only)
+    // LDS tiles won: bands swept together, a contiguous part of that order per
+    // XCD (short columns: the default's only)
     const Shape base = resolve_shape(o, dtype, nlev, mesh->host.V, bs);
     const int sweeps[] = {4, 8, 16};
     for (int b : sweeps) {
       if (nlev <= 32) break;
       Shape s = base;
       s.run_nodes = b;
+      s.xcd_remap = 1;
       if ((rc = time_shape(s))) goto done;
     }
     shape_out(bs, best);

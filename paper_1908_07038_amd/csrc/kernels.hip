@@ -3063,9 +3063,6 @@ Shape resolve_path(int op, int dtype, int nlev, int64_t V, const Shape& sh) {
   // FP64 one-pass gradient and Laplacian: one slice per step fits 16 waves
   // in 128 registers (7.1 ms against 7.7 ms with two slices and 8 waves)
   if (op == OP_GRADLAP && dtype == DT_F64 && !e.slices_per_iter) e.slices_per_iter = 1;
-  // one band of rows at a time, around the whole latitude circle (see
-  // resolve_shape)
-  if (!e.run_nodes) e.run_nodes = op == OP_GRADLAP && dtype == DT_F64 ? kDefaultTileSweep : 1;
   return e;
 }
 
@@ -3095,12 +3092,20 @@ Shape resolve_path(int op, int dtype, int nlev, int64_t V, const Shape& sh) {
 // eighths and 8-band sweeps: O640 x 137 1837 us against 1931 with the schedule
 // and 1984 in plain order (all with its blocks of two nodes; x 60 827 against
 // 837 and 924).
+// Shapes that name the form and no order take the same; a sweep of several
+// bands (run_nodes) in plain order or by the schedule only changes where the
+// tiles are cut, and is ahead of eighths of it too (64 KiB tiles of four rows,
+// 8 waves, sweeps of eight: gradient 589 us against 629, divergence 588
+// against 643; single bands 565 and 578).
 // The other paths, without a tile's reuse of its own halo, keep the eighths.
 Shape resolve_shape(int op, int dtype, int nlev, int64_t V, const Shape& sh) {
   Shape e = resolve_path(op, dtype, nlev, V, sh);
+  const bool one_tile = e.lds_tiles == 3 && uses_tiles(op, dtype, nlev, e);
+  if (one_tile && !e.run_nodes && (sh.lds_tiles == 0 || e.xcd_remap < 0))
+    e.run_nodes = op == OP_GRADLAP && dtype == DT_F64 ? kDefaultTileSweep : 1;
   if (e.xcd_remap >= 0) return e;
   const int k = kernel_op(op);
-  if (!(e.lds_tiles == 3 && uses_tiles(op, dtype, nlev, e))) e.xcd_remap = 1;
+  if (!one_tile) e.xcd_remap = 1;
   else if (op == OP_GRADLAP && dtype == DT_F64) e.xcd_remap = 1;
   else e.xcd_remap = k == OP_GRAD || k == OP_DIVT || dtype == DT_BF16 ? 0 : kXcdSchedule;
   return e;

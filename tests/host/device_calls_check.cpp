@@ -273,6 +273,34 @@ static void described_kernels() {
       }
 }
 
+// Orders of one-tile workgroups: shapes that ask for the form alone go around
+// single bands as the library's own do, and the autotuner's sweeps of several
+// bands are timed in the order that they change, a part of it per XCD.
+static void tile_orders() {
+  Mesh m("O33");
+  for (uint32_t op : {ATLAS_OP_GRADIENT, ATLAS_OP_DIVERGENCE, ATLAS_OP_LAPLACIAN})
+    for (int dt : {ATLAS_F64, ATLAS_F32, ATLAS_BF16}) {
+      atlas_tune_t own{}, t{}, got{};
+      EXPECT(atlas_nabla_describe(m.h, dt, op, 60, &own, nullptr, 0) == ATLAS_OK);
+      t.lds_tiles = 3;
+      EXPECT(atlas_nabla_set_tune(m.h, dt, op, &t) == ATLAS_OK);
+      EXPECT(atlas_nabla_describe(m.h, dt, op, 60, &got, nullptr, 0) == ATLAS_OK);
+      EXPECT(own.run_nodes == 1 && got.run_nodes == own.run_nodes && got.xcd_remap == own.xcd_remap);
+      // a sweep that is asked for stays
+      t.run_nodes = 8;
+      EXPECT(atlas_nabla_set_tune(m.h, dt, op, &t) == ATLAS_OK);
+      EXPECT(atlas_nabla_describe(m.h, dt, op, 60, &got, nullptr, 0) == ATLAS_OK && got.run_nodes == 8);
+      EXPECT(atlas_nabla_set_tune(m.h, dt, op, nullptr) == ATLAS_OK);
+    }
+  atlas_tune_t best{};
+  dev().orders.clear();
+  EXPECT(atlas_nabla_tune(m.h, ATLAS_F32, ATLAS_OP_DIVERGENCE, 60, field(0), field(1), 1, nullptr, &best, nullptr) ==
+         ATLAS_OK);
+  int eighths = 0;
+  for (int r : dev().orders) eighths += r == 1;
+  EXPECT(eighths == 3 * 2);   // three sweeps, a warm-up launch and a timed one each
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> scenarios = {
       {"short_columns_out_of_memory", short_columns_out_of_memory},
@@ -282,6 +310,7 @@ int main(int argc, char** argv) {
       {"plan_out_of_memory", plan_out_of_memory},
       {"field_plan_pair", field_plan_pair},
       {"described_kernels", described_kernels},
+      {"tile_orders", tile_orders},
   };
   if (argc != 2 || !scenarios.count(argv[1])) return 2;
   scenarios.at(argv[1])();

@@ -29,6 +29,7 @@ struct FakeDevice {
   // kernels
   std::map<const void*, std::string> names;
   std::vector<std::string> launches;
+  std::vector<int> orders;             // of the k_tile launches: their `remap` argument
   hipError_t last = hipSuccess;
   int stream_count = 0;
 
@@ -92,8 +93,9 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* s, hipStream_t* s
   *st = fake_stream;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t) {
   dev().launches.push_back(dev().names.count(f) ? dev().names[f] : "?");
+  if (dev().launches.back().rfind("k_tile<", 0) == 0) dev().orders.push_back(*static_cast<int*>(args[2]));
   return hipSuccess;
 }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
