@@ -1445,7 +1445,8 @@ int plan_op(atlas_batch_s* b, int o, BatchOp& bo, bool pair = false) {
     d.U = tile_slices(d.KL, sh);
     bo.umax = std::max(bo.umax, d.U);
     d.nitems = dt.ntiles * d.nchunks;
-    lds = std::max(lds, (int64_t)dt.lds_bytes + tile_tail_bytes(k, b->dtype, d.KL, d.L, d.U));
+    lds = std::max(lds, (int64_t)dt.lds_bytes + tile_tail_bytes(k, b->dtype, d.KL, d.L, d.U,
+                                                               TileForm::kBatched));
     for (int x = 0; x < 8; ++x) {
       const int64_t share = (x + 1) * d.nitems / 8 - x * d.nitems / 8;
       const int64_t next = (int64_t)pre[x * (ntr + 1) + t] + share;

@@ -1662,7 +1662,8 @@ __device__ __forceinline__ void lds_barrier() {
 // blocks); a body of its own, since tile_short next to tile_block raises the
 // register count of the long columns' kernels (FP64 gradient and Laplacian at
 // O1280 x 137 7.1 -> 8.4 ms, BF16 divergence at O640 x 137 430 -> 523 us).
-template <class S, int OP, int U, bool SHORT, class F>
+// BLK: blocks, where the type and operator have them.
+template <class S, int OP, int U, bool SHORT, bool BLK, class F>
 __device__ __forceinline__ void tile_work(const TileArgs& a, int64_t tile, int chunk, char* lds, int W, int wave,
                                           int lane, F&& after_copy) {
   using R = TileRec<S, OP>;
@@ -1682,7 +1683,7 @@ __device__ __forceinline__ void tile_work(const TileArgs& a, int64_t tile, int c
   const int rem = klc & 63;
   const bool pack = rem != 0 && rem <= 32;
   const int kmain = pack ? klc - rem : klc;
-  if constexpr (kUseBlk<S, OP, U>) {
+  if constexpr (BLK && kUseBlk<S, OP, U>) {
     constexpr int NB = kBlkN<S, OP>;
     const int tj = pack ? lane / rem : 0, tt = pack ? lane - tj * rem : 0;   // packed pass: node and level of the lane
     int32_t n0 = 0, q = wave;
@@ -1731,7 +1732,7 @@ __global__ __launch_bounds__((kTileThreads<S, OP, U>), (kTileMinWaves<S, OP, U>)
   const int W = blockDim.x >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  tile_work<S, OP, (U ? U : 1), U == 0>(a, tile, chunk, lds, W, wave, lane, [] {});
+  tile_work<S, OP, (U ? U : 1), U == 0, true>(a, tile, chunk, lds, W, wave, lane, [] {});
 }
 
 // Persistent form over many fields (tracers) of one operator, each on its
@@ -1761,6 +1762,22 @@ __global__ __launch_bounds__((kTileThreads<S, OP, U>), (kTileMinWaves<S, OP, U>)
 template <class S, int OP>
 constexpr int kBatchedThreads = (sizeof(S) == 8 && OP == OP_DIVCURL) ? 512 : 1024;
 inline int batched_max_waves(int kop, int dtype) { return (dtype == DT_F64 && kop == OP_DIVCURL) ? 8 : 16; }
+
+// Blocks in the batched kernel, by the tracer's slices per step.  One kernel
+// holds the code of every slice count of the plan under one register bound, so
+// blocks stay where they gain there: not in the FP64 divergence and gradient
+// adjoint, which would spill under 128 registers (2 and 43 of them with two
+// and three slices), nor in longer steps of the FP64 pair and of FP32
+// scalar-input operators; the short columns' body, one more, in none.  O160,
+// five to twelve tracers of one depth, no blocks / blocks and short body
+// everywhere / this: FP64 divergence x 10 72 / 76 / 71 us, x 19 122 / 134 /
+// 122, x 180 671 / 684 / 674; FP64 pair x 60 491 / 469 / 467, x 180 822 / 872 /
+// 814; all four FP32 operators x 10 211 / 237 / 215, x 60 703 / 680 / 685;
+// FP32 gradient x 180 311 / 321 / 311, FP32 divergence x 60 207 / 186 / 185.
+template <class S, int OP, int U>
+constexpr bool kBatchedBlk = OP == OP_DIV || OP == OP_GRADT ? sizeof(S) == 4
+                             : sizeof(S) == 8               ? OP != OP_DIVCURL || U == 1
+                                                            : U < 3;
 
 template <class S, int OP, int UMAX>
 __global__ __launch_bounds__((kBatchedThreads<S, OP>)) void k_tile_batched(TileArgs base, const BatchTile* __restrict__ tr,
@@ -1837,11 +1854,10 @@ __global__ __launch_bounds__((kBatchedThreads<S, OP>)) void k_tile_batched(TileA
     };
     // UMAX: the largest slice count of the plan's tracers; only the paths
     // up to it are compiled in, which keeps the kernel's code small
-    constexpr bool kShort = kUseBlk<S, OP, 1>;
-    if (kShort && a.KL <= 32) tile_work<S, OP, 1, kShort>(a, tile, chunk, lds, W, wave, lane, advance);
-    else if (UMAX == 1 || U == 1) tile_work<S, OP, 1, false>(a, tile, chunk, lds, W, wave, lane, advance);
-    else if (UMAX == 2 || U == 2) tile_work<S, OP, (UMAX < 2 ? UMAX : 2), false>(a, tile, chunk, lds, W, wave, lane, advance);
-    else tile_work<S, OP, UMAX, false>(a, tile, chunk, lds, W, wave, lane, advance);
+    constexpr int U2 = UMAX < 2 ? UMAX : 2;
+    if (UMAX == 1 || U == 1) tile_work<S, OP, 1, false, kBatchedBlk<S, OP, 1>>(a, tile, chunk, lds, W, wave, lane, advance);
+    else if (UMAX == 2 || U == 2) tile_work<S, OP, U2, false, kBatchedBlk<S, OP, U2>>(a, tile, chunk, lds, W, wave, lane, advance);
+    else tile_work<S, OP, UMAX, false, kBatchedBlk<S, OP, UMAX>>(a, tile, chunk, lds, W, wave, lane, advance);
     // every wave is done reading the buffer, and next_item is written; the
     // tile's output stores need not have landed
     lds_barrier();
@@ -3191,15 +3207,15 @@ int tile_slices(int KL, const Shape& sh) {
   return u < nsl ? u : nsl;
 }
 
-int64_t tile_tail_bytes(int op, int dtype, int KL, int nlev, int U, bool one_tile) {
+int64_t tile_tail_bytes(int op, int dtype, int KL, int nlev, int U, TileForm form) {
   const int64_t es = dtype == DT_F64 ? 8 : dtype == DT_BF16 ? 2 : 4;
   const int64_t cin = (kernel_op(op) == OP_DIV || kernel_op(op) == OP_GRADT || kernel_op(op) == OP_DIVCURL) ? 2 : 1;
   // a step reads 64 levels a slice (U slices, blocks at most kBlkU, other nodes
-  // down to one) from level 0 on, in the one-tile form without the levels of
-  // the packed pass
-  const int64_t step = 64 * (int64_t)(one_tile ? tile_step_slices(op, dtype, U) : U);
+  // down to one) from level 0 on, without the levels of the packed pass of the
+  // forms that have one
+  const int64_t step = 64 * (int64_t)tile_step_slices(op, dtype, U, form);
   auto past = [&](int64_t k) -> int64_t {
-    const int64_t rem = k & 63, kmain = one_tile && rem != 0 && rem <= 32 ? k - rem : k;
+    const int64_t rem = k & 63, kmain = form != TileForm::kPersistent && rem != 0 && rem <= 32 ? k - rem : k;
     const int64_t end = (kmain + step - 1) / step * step;
     return end > k ? end - k : 0;
   };
@@ -3226,11 +3242,14 @@ int with_block_op(int op, int dtype, F&& f) {
 }
 }  // namespace
 
-int tile_step_slices(int op, int dtype, int U) {
+int tile_step_slices(int op, int dtype, int U, TileForm form) {
+  if (form == TileForm::kPersistent) return U;
   return with_block_op(op, dtype, [&](auto tag, auto k) -> int {
     using S = decltype(tag);
     constexpr int OP = decltype(k)::value;
-    const bool blocks = U > 1 ? kUseBlk<S, OP, 2> : kUseBlk<S, OP, 1>;
+    bool blocks = U > 1 ? kUseBlk<S, OP, 2> : kUseBlk<S, OP, 1>;
+    if (form == TileForm::kBatched)
+      blocks &= U == 1 ? kBatchedBlk<S, OP, 1> : U == 2 ? kBatchedBlk<S, OP, 2> : kBatchedBlk<S, OP, 3>;
     return blocks && U > kBlkU<S, OP> ? kBlkU<S, OP> : U;
   });
 }
@@ -3337,7 +3356,7 @@ hipError_t launch_tiles(int op, int dtype, const DevTiles& dt, const void* rec, 
   int U = shape.slices_per_iter > 0 ? shape.slices_per_iter : 3;
   if (U > nsl) U = nsl;
   // whole-wave nodes read past a column's last level, as in the one-tile form
-  const uint32_t lds = 2 * buf_bytes + (P == 64 ? (uint32_t)tile_tail_bytes(op, dtype, dt.KL, nlev, U, false) : 0u);
+  const uint32_t lds = 2 * buf_bytes + (P == 64 ? (uint32_t)tile_tail_bytes(op, dtype, dt.KL, nlev, U, TileForm::kPersistent) : 0u);
   // workgroups per CU as asked, as far as their two buffers fit the CU's LDS
   int per_cu = shape.tile_wgs_per_cu > 0 ? shape.tile_wgs_per_cu : 1;
   while (per_cu > 1 && (uint64_t)lds * per_cu > kLdsPerCu) --per_cu;

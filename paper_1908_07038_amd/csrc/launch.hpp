@@ -138,15 +138,17 @@ TileGeom tile_geom(int op, int dtype, int nlev, const Shape& sh);
 int64_t tile_record_bytes(int op, int dtype);
 // Nodes a wave evaluates together where their stencils have the regular shape.
 int tile_block_nodes(int op, int dtype);
-// Slices of 64 levels the longest step of the one-tile form reads at a time
-// when launched with U of them: blocks take fewer than U.
-int tile_step_slices(int op, int dtype, int U);
+// One tile per workgroup, the batched kernel, or the double-buffered persistent
+// form (whose nodes have no blocks and no packed pass).
+enum class TileForm { kOneTile, kBatched, kPersistent };
+// Slices of 64 levels the longest step reads at a time when launched with U of
+// them: blocks take fewer than U.
+int tile_step_slices(int op, int dtype, int U, TileForm form);
 // LDS bytes kept free behind a workgroup's tile buffers: lanes past a column's
 // last level read (and drop) values beyond it, up to the end of the step
-// (chunks of KL levels, the last one shorter; U slices a step; one_tile: the
-// one-tile and batched forms, whose blocks step over tile_step_slices and
-// whose packed pass reads no further than the column).
-int64_t tile_tail_bytes(int op, int dtype, int KL, int nlev, int U, bool one_tile = true);
+// (chunks of KL levels, the last one shorter; U slices a step; the packed pass
+// reads no further than the column).
+int64_t tile_tail_bytes(int op, int dtype, int KL, int nlev, int U, TileForm form = TileForm::kOneTile);
 // Level slices per step of the one-tile form for chunks of KL levels: the
 // whole 64-level slices (a remainder of 1..32 levels is evaluated in a packed
 // pass, several nodes to a wave), at most 3 or slices_per_iter.

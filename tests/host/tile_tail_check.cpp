@@ -4,8 +4,10 @@
 // two 64-level slices (one in the FP64 two-ring and the BF16 pairs, which have
 // no blocks on longer steps), the nodes outside the blocks over one; kernels
 // without blocks over the launch's slices, their nodes of other degrees over
-// one.  A remainder of 1..32 levels is read without running past it.
-// Usage: tile_tail_check N nlev
+// one.  A remainder of 1..32 levels is read without running past it.  In the
+// batched kernel the FP64 divergence and gradient adjoint have no blocks, the
+// FP64 pair only on one slice, FP32 scalar inputs only on one and two.
+// Usage: tile_tail_check N nlev one|batched
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -17,7 +19,8 @@
 using namespace atlasnabla;
 
 int main(int argc, char** argv) {
-  if (argc != 3) return 2;
+  if (argc != 4) return 2;
+  const bool batched = argv[3][0] == 'b';
   const int N = std::atoi(argv[1]), L = std::atoi(argv[2]);
   HostMesh m;
   build_host_mesh(N, 6371220.0, m);
@@ -25,12 +28,15 @@ int main(int argc, char** argv) {
   build_op_tables(m, t);
   const int ops[] = {OP_GRAD, OP_DIV, OP_GRADT, OP_DIVT, OP_LAP, OP_CURL, OP_CURLT, OP_GRADLAP, OP_DIVCURL, OP_DIVGRADT};
   int bad = 0;
-  for (int dtype = 0; dtype < 3; ++dtype)
+  for (int dtype = 0; dtype < (batched ? 2 : 3); ++dtype)
     for (int op : ops)
-      for (int slices = 0; slices <= 3; ++slices) {
+      for (int k = 0; k < 8; ++k) {
+        const int slices = k & 3;
         Shape ask;
         ask.slices_per_iter = slices;
+        ask.tile_kb = k < 4 ? 0 : 160;   // the default, and whole columns up to some hundred levels
         const Shape sh = resolve_shape(op, dtype, L, m.V, ask);
+        if (batched && op >= OP_LAP && op != OP_DIVGRADT) continue;
         if (sh.lds_tiles != 3 || !uses_tiles(op, dtype, L, sh)) continue;
         const TileGeom g = tile_geom(op, dtype, L, sh);
         if (g.KL < 1) continue;
@@ -45,14 +51,15 @@ int main(int argc, char** argv) {
         int64_t tile_lds = 0;
         for (int64_t tl = 0; tl < ht.ntiles; ++tl)
           tile_lds = std::max(tile_lds, ht.info[4 * tl + 2] * g.col_bytes + ht.info[4 * tl + 3] * g.row_bytes);
-        const int64_t lds = tile_lds + (bf ? 16 : 0) + tile_tail_bytes(op, dtype, g.KL, L, U);
+        const int64_t lds = tile_lds + (bf ? 16 : 0) + tile_tail_bytes(op, dtype, g.KL, L, U, batched ? TileForm::kBatched : TileForm::kOneTile);
         if (lds > 160 * 1024) ++bad;
-        const bool blocks = g.block > 0 && !(bf && dual && U > 1);
+        const bool in_batched = dtype == DT_F64 ? cin == 1 || (dual && U == 1) : cin == 2 || U < 3;
+        const bool blocks = g.block > 0 && !(bf && dual && U > 1) && (!batched || in_batched);
         const int bu = (dtype == DT_F64 && two) || (bf && dual) ? 1 : 2;
         int64_t worst = 0, over = 0;
         for (int klc : {g.KL, L - (L - 1) / g.KL * g.KL}) {
           const int rem = klc & 63, kmain = rem != 0 && rem <= 32 ? klc - rem : klc;
-          if (kmain == 0 || (blocks && g.KL <= 32)) continue;
+          if (kmain == 0) continue;
           auto upto = [&](int64_t step) { return (kmain + 64 * step - 1) / (64 * step) * 64 * step; };
           for (int64_t tl = 0; tl < ht.ntiles; ++tl) {
             const int n = ht.info[4 * tl + 3];

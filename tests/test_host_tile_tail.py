@@ -26,8 +26,9 @@ def checker():
     return exe
 
 
+@pytest.mark.parametrize("form", ["one", "batched"])
 @pytest.mark.parametrize("L", [33, 63, 64, 96, 97, 127, 128, 137, 160, 161, 180, 191, 192, 193, 224, 225, 256, 320,
                                384, 545, 576, 700])
-def test_reads_end_inside_the_request(checker, L):
-    r = subprocess.run([checker, "33", str(L)], capture_output=True, text=True, timeout=600)
+def test_reads_end_inside_the_request(checker, L, form):
+    r = subprocess.run([checker, "33", str(L), form], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0 and r.stdout.strip().endswith("OK"), r.stdout + r.stderr
