@@ -141,8 +141,9 @@ void build_halo_tiles(const HostMesh& m, const OpTables& t, int ring, int band_r
 void group_blocks(const OpTables& t, int block_nodes, HaloTiles& ht, std::vector<int32_t>& nblk);
 
 // Tiles by XCD: entry 8 i + x of sched (four int32 each, copied from info) is
-// the i-th tile XCD x takes; entries of zeros are holes.  Band by band, each
-// XCD takes an eighth of the band's tiles, side by side in longitude.
+// the i-th tile XCD x takes; entries of zeros are holes, in the last rounds
+// only.  Band by band, each XCD takes an eighth of the band's tiles, side by
+// side in longitude, so that the nodes of all XCDs stay alike.
 void schedule_tiles(const HostMesh& m, const HaloTiles& ht, const std::vector<int32_t>& info, int band_rows,
                     std::vector<int32_t>& sched);
 

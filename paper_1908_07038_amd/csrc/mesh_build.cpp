@@ -822,15 +822,40 @@ void schedule_tiles(const HostMesh& m, const HaloTiles& ht, const std::vector<in
   std::vector<std::vector<int64_t>> band((m.nrows + band_rows - 1) / band_rows);
   for (int64_t t = 0; t < ht.ntiles; ++t)
     band[m.node_row[ht.order[ht.info[4 * t + 1]]] / band_rows].push_back(t);
-  sched.clear();
+  // the eighths of n tiles may start at any of eight remainders, which decides
+  // who takes the tiles left over: the one that leaves the XCDs' nodes so far
+  // most alike
+  std::vector<int64_t> list[kXcds];
+  int64_t load[kXcds] = {};
   for (const auto& b : band) {
     const int64_t n = (int64_t)b.size();
-    for (int64_t i = 0; i < (n + kXcds - 1) / kXcds; ++i)
+    auto from = [&](int64_t x, int64_t r) { return (n * x + r) / kXcds; };
+    int64_t best = 0;
+    double least = 0;
+    for (int64_t r = 0; r < kXcds; ++r) {
+      double squares = 0;
       for (int64_t x = 0; x < kXcds; ++x) {
-        const int64_t t = n * x / kXcds + i;
-        for (int q = 0; q < 4; ++q) sched.push_back(t < n * (x + 1) / kXcds ? info[4 * b[t] + q] : 0);
+        double l = (double)load[x];
+        for (int64_t t = from(x, r); t < from(x + 1, r); ++t) l += ht.info[4 * b[t] + 3];
+        squares += l * l;
+      }
+      if (r == 0 || squares < least) {
+        best = r;
+        least = squares;
+      }
+    }
+    for (int64_t x = 0; x < kXcds; ++x)
+      for (int64_t t = from(x, best); t < from(x + 1, best); ++t) {
+        list[x].push_back(b[t]);
+        load[x] += ht.info[4 * b[t] + 3];
       }
   }
+  size_t rounds = 0;
+  for (const auto& l : list) rounds = std::max(rounds, l.size());
+  sched.clear();
+  for (size_t i = 0; i < rounds; ++i)
+    for (const auto& l : list)
+      for (int q = 0; q < 4; ++q) sched.push_back(i < l.size() ? info[4 * l[i] + q] : 0);
 }
 
 }  // namespace atlasnabla
