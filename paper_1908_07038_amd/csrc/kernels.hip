@@ -3100,10 +3100,13 @@ Shape resolve_path(int op, int dtype, int nlev, int64_t V, const Shape& sh) {
 // so tiles side by side share their halo columns in one L2, where that halo
 // is wide: two columns each side (the two-ring operators: FP32 Laplacian 580
 // -> 553 us, gradient and Laplacian 915 -> 872) or two
-// components (divergence 599 -> 571 us FP32, 1.35 -> 1.31 ms FP64).  The
-// scalar-input 1-ring operators lose by it (FP64 gradient 1.10 -> 1.15 ms), so
-// do most BF16 columns, half as wide (gradient 330 -> 344 us, divergence and
-// curl 368 -> 382 at 91 levels): they keep the plain order.
+// components (divergence 599 -> 571 us FP32, 1.35 -> 1.31 ms FP64; BF16 376 ->
+// 363, Laplacian 441 -> 429, gradient 329 -> 319).  The FP32 and FP64
+// scalar-input 1-ring operators gain by it while the GPU's caches still hold
+// much of the field (FP64 gradient O100 x 200 48.3 -> 39.1 us, O320 x 200, 0.67
+// GB, 439 -> 429; FP32 O200 x 97 40.7 -> 35.6, O640 x 91, 0.6 GB, 371 -> 362) and
+// lose on larger ones (FP64 O640 x 60, 0.8 GB, 474 -> 491, x 137 1.10 -> 1.14
+// ms; FP32 O1280 x 137 2.18 -> 2.26): those keep the plain order.
 // The FP64 one-pass gradient and Laplacian, one 160 KiB tile per CU, keeps the
 // eighths and 8-band sweeps: O640 x 137 1837 us against 1931 with the schedule
 // and 1984 in plain order (all with its blocks of two nodes; x 60 827 against
@@ -3123,7 +3126,8 @@ Shape resolve_shape(int op, int dtype, int nlev, int64_t V, const Shape& sh) {
   const int k = kernel_op(op);
   if (!one_tile) e.xcd_remap = 1;
   else if (op == OP_GRADLAP && dtype == DT_F64) e.xcd_remap = 1;
-  else e.xcd_remap = k == OP_GRAD || k == OP_DIVT || dtype == DT_BF16 ? 0 : kXcdSchedule;
+  else if (dtype == DT_BF16 || (k != OP_GRAD && k != OP_DIVT)) e.xcd_remap = kXcdSchedule;
+  else e.xcd_remap = V * nlev * (dtype == DT_F64 ? 8 : 4) <= kScheduleBytes ? kXcdSchedule : 0;
   return e;
 }
 

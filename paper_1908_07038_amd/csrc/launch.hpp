@@ -67,6 +67,7 @@ struct Shape {
 };
 
 constexpr int kXcdSchedule = 2;
+constexpr int64_t kScheduleBytes = int64_t(700) << 20;   // largest FP32/FP64 scalar input whose 1-ring tiles take it
 constexpr int kShortTileLevels = 8;             // fewest levels and values (nodes x levels) of a field of
 constexpr int64_t kShortTileValues = 5 << 19;   // columns of at most 32 levels that takes LDS tiles
 // Part of the device's memory that the tables of short columns may reach on a
