@@ -50,7 +50,7 @@ OP_ELEMS = {"gradient": (1, 2), "divergence": (2, 1), "laplacian": (1, 1), "grad
             "divergence_gradient_adjoint": (2, 2)}
 OP_SWEEPS = {"gradient": 1, "divergence": 1, "laplacian": 2, "gradient_laplacian": 3, "gradient_adjoint": 1,
              "divergence_adjoint": 1, "conservation": 0, "divergence_gradient_adjoint": 2}
-CONSERVATION_KERNELS = "k_cons_flat (FP64: k_cons_partial) + k_cons_final"
+CONSERVATION_KERNELS = "k_cons_flat + k_cons_final"
 
 
 def kernel_names(pa, mesh, dtype_code, L):

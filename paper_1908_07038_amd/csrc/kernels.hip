@@ -2585,10 +2585,16 @@ __global__ __launch_bounds__(64 * kConsWaves) void k_cons_partial(const S* __res
 // are one run of memory.  At the end the g sums of a level are combined in
 // node order, in two stages.  ALN: the field is 16-byte aligned; else the
 // same numbers are loaded one at a time.  Bound by memory reads; one
-// workgroup of 16 waves per CU, which keeps the partial sums few (1024
-// workgroups: O640 x 19 FP32 42 us, 256: 30).  Slices of 64 levels -> this:
-// O1280 x 137 FP32 694 -> 661 us (5.5 TB/s), BF16 617 -> 335, O640 x 91 FP32
-// 152 -> 114, x 19 113 -> 30, x 2 106 -> 21, O320 x 60 FP64 44 -> 39.
+// workgroup of 8 waves per CU (BF16, with twice the numbers a load to widen, of
+// 16 where its part of the field has eight groups or more), which keeps the
+// partial sums few (512 workgroups: O640 x 19 FP32 27.4 us, 256: 25.9) and the
+// groups short: of 16 waves FP32 and FP64 are slower throughout, the more so
+// where a step of all groups is 256 bytes short of 64 KiB (60 and 120 levels:
+// O640 x 120 FP32 204 us against 138, 165 in slices).  BF16 with 8 waves O100 x
+// 137 12.6 -> 11.0 us, O640 x 137 92 -> 139.  Slices of 64 levels -> this:
+// O1280 x 137 FP32 692 -> 633 us (5.7 TB/s), FP64 1.23 -> 1.12 ms, BF16 615 ->
+// 337 us, O640 x 91 FP32 152 -> 111, x 19 110 -> 26, FP64 x 60 154 -> 131, O320
+// x 60 FP64 41 -> 34.
 constexpr int kConsFlatLevels = 1024;
 constexpr int kConsFlatThreads = 1024;
 constexpr int kConsFlatParts = 256;   // most workgroups: one per CU
@@ -3439,18 +3445,21 @@ hipError_t launch_conservation(int dtype, const double* vol, int64_t V, int nlev
   int parts = conservation_parts(V, nlev);
   const int64_t es = dtype == DT_F64 ? 8 : dtype == DT_F32 ? 4 : 2;
   const int64_t vec = es == 2 ? 8 : 4;
-  // the flat form, but for FP64 fields of over 2 GiB, where the slices are
-  // ahead (O1280 x 137: 1.23 ms against 1.30; O640 x 137, 1.8 GB: 334 us
-  // against 328)
-  const bool large64 = es == 8 && V * nlev > (int64_t)1 << 28;
-  if (nlev <= kConsFlatLevels && V % vec == 0 && !large64) {
+  if (nlev <= kConsFlatLevels && V % vec == 0) {
     if (parts > kConsFlatParts) parts = kConsFlatParts;
-    // nodes of a group: as many as the threads hold, no more than a
-    // workgroup's part, in steps that keep whole vectors
+    // nodes of a group: as many as 8 waves hold (BF16 16 where the part has
+    // eight such groups), no more than a workgroup's part, in steps that keep
+    // whole vectors
     int64_t q = vec;
     while (q > 1 && (q / 2) * nlev % vec == 0) q /= 2;
-    const int64_t most = kConsFlatThreads * vec / nlev / q * q, part = ((V + parts - 1) / parts + q - 1) / q * q;
-    const int64_t gn = most < part ? most : part;
+    const int64_t part = ((V + parts - 1) / parts + q - 1) / q * q;
+    auto fit = [&](int64_t threads) {
+      int64_t n = threads * vec / nlev / q * q;
+      if (n < q) n = q;
+      return n < part ? n : part;
+    };
+    int64_t gn = fit(kConsFlatThreads);
+    if (es != 2 || part < 8 * gn) gn = fit(kConsFlatThreads / 2);
     const int64_t thr = (gn * nlev / vec + 63) / 64 * 64;
     const int threads = (int)(thr > (nlev + 63) / 64 * 64 ? thr : (nlev + 63) / 64 * 64);
     const bool aln = ((uintptr_t)div & 15u) == 0;
