@@ -3068,12 +3068,14 @@ Shape resolve_path(int op, int dtype, int nlev, int64_t V, const Shape& sh) {
   else if (dtype == DT_BF16)
     d = lap ? Def{3, 53, 4, 0, 0, 0, 8} : vec_in ? Def{3, 80, 4, 0, 0, 0, 16} : Def{3, 64, 4, 0, 0, 0, 16};
   else
-    d = lap    ? Def{3, 160, op == OP_LAP ? 6 : 4, 0, 0, 0, 16}
+    d = lap    ? Def{3, 160, op == OP_LAP && V * nlev >= kTallTileValues ? 6 : 4, 0, 0, 0, 16}
         : dual ? Def{3, 160, 4, 0, 0, 0, 8}
         : vec_in ? Def{3, 80, 4, 0, 0, 0, 8}
                  : Def{3, 64, 3, 0, 0, 0, 8};
   // (FP64 Laplacian: tiles of six rows, 1.24 ms at O640 x 137, against 1.30
-  // with four)
+  // with four, O160 x 91 64.6 us against 66.2; but on small fields, where they
+  // leave CUs without a tile, 10.7 against 9.5 at O32 x 91, 40.6 against 39.5 at
+  // O100 x 137)
   e.lds_tiles = d.mode;
   if (d.mode == 2) return e;
   if (!e.tile_kb) e.tile_kb = d.kb;

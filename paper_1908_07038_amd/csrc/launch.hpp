@@ -79,6 +79,7 @@ constexpr int kDefaultRunNodes = 16;
 constexpr int kDefaultWindowRunNodes = 64;
 constexpr int kDefaultTileKB = 48;
 constexpr int kDefaultTileRows = 4;    // LDS tiles: rows per tile (band_rows)
+constexpr int64_t kTallTileValues = 1 << 23;   // values (nodes x levels) from which FP64 Laplacian tiles take six
 constexpr int kDefaultBatchClaim = 4;  // batched persistent form: tiles per work claim
 constexpr int64_t kBatchFieldValues = 5 << 22;   // batched plans: values per tracer from which field launches are the default
 constexpr int kBatchFieldCounts = 8;             // ... and the most different level counts (each has its own tables)
