@@ -906,11 +906,19 @@ __device__ __forceinline__ void tile_node2(const TileArgs& a, const char* lds, c
   for (int kb = 64 * U; kb < klc; kb += 64 * U) step(kb);
 }
 
+// Difference of entry s as the gradient takes it (every node has three
+// neighbours; pairs of zeros past its degree).
+template <class C, class C2>
+__device__ __forceinline__ C grad_diff(int s, C2 pair, C d) {
+  return s >= 3 && pair.x == 0 && pair.y == 0 ? C(0) : d;
+}
+
 // One node of the fused gradient and two-ring Laplacian (OP_GRADLAP): the
 // differences f_m - f_i of the NS entries feed both sums; the first 7 entries
 // are the node's 1-ring neighbours in slot order (the two-ring tables are
 // ordered so), weighted by the gradient pairs (zero past the node's degree,
-// which add exact zeros).  Same slot-order arithmetic as tile_node2 and the
+// where the entry is of the second ring and its difference is taken as zero:
+// it need not be finite).  Same slot-order arithmetic as tile_node2 and the
 // gradient's tile_node1.
 template <class S, int U, int NS>
 __device__ __forceinline__ void tile_node2g(const TileArgs& a, const char* lds, const uint32_t* so, uint32_t xo,
@@ -945,8 +953,9 @@ __device__ __forceinline__ void tile_node2g(const TileArgs& a, const char* lds, 
         const C d = v[u][s] - x0[u];
         acc[u] = fma(w[s], d, acc[u]);
         if (s < 7) {
-          ax[u] = fma(cf[s].x, d, ax[u]);
-          ay[u] = fma(cf[s].y, d, ay[u]);
+          const C e = grad_diff<C>(s, cf[s], d);
+          ax[u] = fma(cf[s].x, e, ax[u]);
+          ay[u] = fma(cf[s].y, e, ay[u]);
         }
       }
       keep(acc[u]);
@@ -1450,8 +1459,9 @@ __device__ __forceinline__ void tile_tail(const TileArgs& a, const char* lds, in
           if constexpr (R::kGrad) {
             if (q < 7) {
               const C2 cq = lds_ld<C2>(lds, ro + R::kLapB + q * (uint32_t)sizeof(C2));
-              ax = fma(cq.x, d, ax);
-              ay = fma(cq.y, d, ay);
+              const C e = grad_diff<C>(q, cq, d);
+              ax = fma(cq.x, e, ax);
+              ay = fma(cq.y, e, ay);
             }
           }
         }
