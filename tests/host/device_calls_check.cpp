@@ -301,6 +301,41 @@ static void tile_orders() {
   EXPECT(eighths == 3 * 2);   // three sweeps, a warm-up launch and a timed one each
 }
 
+// Which plans run the tracers' field launches: all-default ones of at least 5 x
+// 2^22 values a tracer and at most eight level counts, on default shapes
+// whatever the mesh's are; with the divergence pair, where nothing overlaps.
+static void plan_rule() {
+  Mesh m("O200");   // 167,200 nodes: 126 levels are past 5 x 2^22
+  EXPECT(m.V * 125 < 5 * (1 << 22) && m.V * 126 >= 5 * (1 << 22));
+  const auto forms = [&](const std::vector<int>& levels, const atlas_tune_t* t, uint32_t ops) {
+    Plan p(m, levels, t, ATLAS_F32, ops);
+    dev().launches.clear();
+    EXPECT(p.rc == ATLAS_OK && atlas_batch_run(p.h, nullptr) == ATLAS_OK);
+    return std::make_pair(dev().count("k_tile<"), dev().count("k_tile_batched<"));
+  };
+  const uint32_t one = ATLAS_OP_GRADIENT;
+  using P = std::pair<int, int>;
+  EXPECT(forms({126, 126}, nullptr, one) == P(2, 0));
+  EXPECT(forms({125, 125}, nullptr, one) == P(0, 1));
+  EXPECT(forms({1, 251}, nullptr, one).second == 0);   // a mean of 126 levels
+  EXPECT(forms({126, 127, 128, 129, 130, 131, 132, 133}, nullptr, one) == P(8, 0));
+  EXPECT(forms({126, 127, 128, 129, 130, 131, 132, 133, 134}, nullptr, one) == P(0, 1));
+  atlas_tune_t t{};
+  t.tile_kb = 64;
+  EXPECT(forms({126, 126}, &t, one) == P(0, 1));
+  t = {};
+  t.batch_mode = 1;
+  EXPECT(forms({126, 126}, &t, one) == P(0, 1));
+  t.batch_mode = 2;
+  EXPECT(forms({5, 33}, &t, one).second == 0);
+  EXPECT(forms({126, 126}, nullptr, 0xF) == P(3 * 2, 0) && dev().count("k_tile<float, 8,") == 2);
+  EXPECT(forms({125, 125}, nullptr, 0xF) == P(0, 3) && dev().count("k_tile_batched<float, 8,") == 1);
+  t = {};
+  t.lds_tiles = 2;
+  EXPECT(atlas_nabla_set_tune(m.h, ATLAS_F32, one, &t) == ATLAS_OK);
+  EXPECT(forms({126, 126}, nullptr, one) == P(2, 0));
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> scenarios = {
       {"short_columns_out_of_memory", short_columns_out_of_memory},
@@ -311,6 +346,7 @@ int main(int argc, char** argv) {
       {"field_plan_pair", field_plan_pair},
       {"described_kernels", described_kernels},
       {"tile_orders", tile_orders},
+      {"plan_rule", plan_rule},
   };
   if (argc != 2 || !scenarios.count(argv[1])) return 2;
   scenarios.at(argv[1])();

@@ -26,7 +26,7 @@ def checker():
 
 @pytest.mark.parametrize("scenario", ["short_columns_out_of_memory", "short_columns_captured",
                                       "short_columns_beside_a_capture", "short_columns_table_budget",
-                                      "plan_out_of_memory", "field_plan_pair", "described_kernels", "tile_orders"])
+                                      "plan_out_of_memory", "field_plan_pair", "described_kernels", "tile_orders", "plan_rule"])
 def test_device_calls(checker, scenario):
     r = subprocess.run([checker, scenario], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.strip().endswith("OK"), r.stdout + r.stderr
