@@ -302,9 +302,9 @@ def run_remap(args, pa, mesh, f64):
 
 def run_batched(args):
     """O640, 64 tracers with level counts drawn from {1, 19, 60, 91, 137}:
-    gradient, divergence and both adjoints of every tracer in one persistent
-    launch per operator, replayed as a HIP graph; against the same chain as
-    single-field calls (default shapes) one tracer at a time."""
+    gradient, divergence and both adjoints of every tracer in one plan,
+    replayed as a HIP graph: autotuned, at its default, and in either form; and
+    the same chain as single-field calls (default shapes) one tracer at a time."""
     import torch
 
     import paper_1908_07038_amd as pa
@@ -347,11 +347,14 @@ def run_batched(args):
         torch.cuda.synchronize()
         return a.elapsed_time(b) / reps
 
-    # the tracers' field launches replayed as a graph, the persistent plan at
-    # its default shape, then the persistent plan after the autotuner
+    # the tracers' field launches and one persistent launch per operator, then
+    # the plan as it comes, and after the autotuner
     fields = pa.Batch(mesh, tracers, tune={"batch_mode": 2})
     t_fields = time_graph(fields)
     fields.close()
+    persistent = pa.Batch(mesh, tracers, tune={"batch_mode": 1})
+    t_persistent = time_graph(persistent)
+    persistent.close()
     plan = pa.Batch(mesh, tracers)
     t_default = time_graph(plan)
     t0 = time.time()
@@ -383,7 +386,8 @@ def run_batched(args):
     by = 10 * 4 * V * sl + 3 * GEOM_BYTES_PER_NODE * V * len(levels)
     out = {"workload": "O640, 64 tracers, levels from {1,19,60,91,137} (seed 1005), FP32: grad, div, "
                        "grad adjoint, div adjoint (div and grad adjoint of the same field as one pass), "
-                       "one persistent launch per operator, graph-replayed, autotuned",
+                       "graph-replayed, autotuned (tuned_shapes: batch_mode 1 one persistent launch per operator, "
+                       "2 the tracers' field launches)",
            "sum_levels": sl, "graph_ms": round(t_graph, 3),
            "edge_updates_s": float(f"{4 * E * sl / (t_graph * 1e-3):.4g}"),
            "alg_GB_s": round(by / (t_graph * 1e-3) / 1e9, 1),
@@ -391,10 +395,11 @@ def run_batched(args):
            "tuned_shapes": tuned,
            "default_shape_graph_ms": round(t_default, 3),
            "field_launch_graph_ms": round(t_fields, 3),
+           "persistent_graph_ms": round(t_persistent, 3),
            "single_field_ms": round(t_single, 3),
            "speedup_over_single_field": round(t_single / t_graph, 3)}
-    log(f"batched: persistent graph {t_graph:.2f} ms (default shape {t_default:.2f}), field-launch graph "
-        f"{t_fields:.2f} ms, single-field calls {t_single:.2f} ms")
+    log(f"batched: tuned graph {t_graph:.2f} ms (default {t_default:.2f}, field launches {t_fields:.2f}, persistent "
+        f"{t_persistent:.2f}), single-field calls {t_single:.2f} ms")
     del tracers, plan
     torch.cuda.empty_cache()
     return out

@@ -303,9 +303,10 @@ int atlas_remap_apply_adjoint(atlas_remap_t remap, int dtype, int32_t nlev, cons
                               void* stream);
 
 /* ---- batched multi-tracer launch ------------------------------------------
- * Many fields with different level counts go through one persistent kernel
- * launch per operator.  Per tracer, the same arithmetic per output element
- * as the single-field calls, so results are bitwise identical to them. */
+ * Many fields with different level counts in one plan: one persistent kernel
+ * launch per operator, or, where the fields are large, the single-field launch
+ * of every tracer.  Either way the same arithmetic per output element as the
+ * single-field calls, so results are bitwise identical to them. */
 
 enum {
   ATLAS_OP_GRADIENT = 1,
@@ -364,7 +365,11 @@ typedef struct {
                                0 the library's own, which also takes 3 for
                                columns of 8 to 32 levels of a field of at
                                least 5 x 2^19 nodes x levels, if the shape
-                               sets no parameter of the other paths           */
+                               sets no parameter of the other paths, while
+                               the tables of such columns (a tiling and
+                               records for each operator and level count)
+                               stay under a sixteenth of the device's memory
+                               a mesh and can be allocated                    */
   int32_t tile_kb;          /* LDS budget of one tile in KiB, 8..160 (0: per-
                                operator default); the persistent form holds
                                two tiles, which must fit the CU's 160 KiB     */
@@ -392,7 +397,8 @@ typedef struct {
                                0 persistent, but for a shape of defaults only
                                on at least 5 x 2^22 nodes x levels a tracer of
                                at most 8 different level counts: field
-                               launches on the default shapes                 */
+                               launches on the default shapes, if the device's
+                               memory holds their tables                      */
   int32_t batch_claim;      /* batched persistent form: consecutive tiles a
                                workgroup takes per claim on its XCD's work
                                counter, 1..64 (0: 4)                          */
@@ -424,11 +430,13 @@ int atlas_batch_create(atlas_mesh_t mesh, int dtype, const atlas_tracer_desc_t* 
  * the divergence's form and shape (as atlas_nabla_divergence_gradient_adjoint:
  * the same values; persistent in FP64 only on shapes of at most 8 waves, else
  * as two launches); atlas_batch_tune still times them one at a time.  The
- * persistent form and the field form on default shapes
- * allocate nothing and never synchronise; with batch_mode 2 a plan does so only the
- * first time a (operator, dtype, level count) is used on the mesh, when it
- * builds node orders, tilings and records -- after one eager run it too may be
- * recorded into a HIP graph by stream capture. */
+ * persistent form and the field form on default shapes allocate nothing and
+ * never synchronise; with batch_mode 2 a plan does so only the first time a
+ * (operator, dtype, level count) is used on the mesh, when it builds node
+ * orders, tilings and records -- after one eager run it too may be recorded
+ * into a HIP graph by stream capture (captured when only the single
+ * operators' tables are there, it runs the divergence and the gradient adjoint
+ * apart). */
 int atlas_batch_run(atlas_batch_t plan, void* stream);
 
 /* Run the plan through a HIP graph owned by the plan: the first call

@@ -6,7 +6,8 @@ workgroups of each XCD walk that XCD's share of the (tracer, tile, level
 chunk) items on the LDS tiles of the single-field one-tile form, with the
 same arithmetic per output element, so results equal the single-field calls
 bit for bit.  ``tune={"batch_mode": 1}`` asks for the persistent form,
-``{"batch_mode": 2}`` for the tracers' single-field launches.  Either form can be replayed as a HIP graph."""
+``{"batch_mode": 2}`` for the tracers' single-field launches.  Either form can
+be replayed as a HIP graph."""
 
 import ctypes
 
@@ -79,7 +80,7 @@ class Batch:
 
     def run(self):
         """Enqueue the plan on the current stream: one persistent launch per
-        operator (or the field launches with ``batch_mode`` 2)."""
+        operator, or the tracers' field launches."""
         _check(lib().atlas_batch_run(self._h, _stream(self.device_tensor)))
 
     def graph_launch(self):

@@ -62,7 +62,7 @@ struct Shape {
   int tile_wgs_per_cu = 0;   // 0: 1; persistent tile workgroups per CU
   int tile_levels = 0;       // 0: automatic; else levels per column chunk of a tile
   bool short_tiles = false;  // set by resolve_shape: columns of at most 32 levels on LDS tiles
-  int batch_mode = 0;        // batched plans: 0 default (persistent), 1 persistent tiled, 2 field launches
+  int batch_mode = 0;        // batched plans: 0 the library's choice, 1 persistent tiled, 2 field launches
   int batch_claim = 0;       // batched persistent form: tiles per work claim (0: kDefaultBatchClaim)
 };
 
@@ -170,11 +170,11 @@ hipError_t launch_tiles(int op, int dtype, const DevTiles& dt, const void* rec, 
 hipError_t launch_op(int op, int dtype, const DevTables& t, const NodeOrder& ord, int64_t V, int nlev,
                      const void* in, void* out, const Shape& shape, hipStream_t stream);
 
-// Conservation sums: partial [nparts][nlev][2] doubles of scratch, then the
-// final fixed-order pass into out_sum/out_abs.
 // out += base (n numbers; BF16 in FP32, rounded once).
 hipError_t launch_add(int dtype, int64_t n, const void* base, void* out, hipStream_t stream);
 
+// Conservation sums: partial [nparts][nlev][2] doubles of scratch, then the
+// final fixed-order pass into out_sum/out_abs.
 int conservation_parts(int64_t V, int nlev);
 hipError_t launch_conservation(int dtype, const double* vol, int64_t V, int nlev,
                                const void* div, double* scratch, double* out_sum,
