@@ -1528,8 +1528,8 @@ __device__ __forceinline__ void tile_tail(const TileArgs& a, const char* lds, in
 // blocks share a wave, lane = (block tj, level tt), each lane with its block's
 // row positions and table rows.  As tile_block, the columns the block's nodes
 // share are read once; table rows come per lane from LDS.  Bound by LDS reads
-// and, FP32 at O640 x 19, by memory: gradient 102 us (4.5 TB/s over the
-// arrays), Laplacian 124.
+// and, FP32 at O640 x 19, by memory: gradient 100 us (4.5 TB/s over the
+// arrays), Laplacian 109.
 template <class S, int OP, int NB>
 __device__ __forceinline__ void tile_short(const TileArgs& a, const char* lds, int32_t nblk, uint32_t data_off,
                                            uint32_t colB, int k0, int rem, int tj, int tt, int wave, int W) {
@@ -3037,17 +3037,17 @@ Shape resolve_path(int op, int dtype, int nlev, int64_t V, const Shape& sh) {
     // Columns of at most 32 levels: the gather gives a wave 64 / nlev nodes
     // and reads each neighbour's column from L2, in pieces of less than a
     // cache line; the tiles read every column once, in whole tiles.  19
-    // levels, gather -> tiles: O640 FP32 gradient 253 -> 102 us, divergence
-    // 303 -> 118, Laplacian 443 -> 124, divergence and curl 603 -> 160; FP64
-    // divergence 426 -> 198, BF16 Laplacian 373 -> 96; 32 levels FP32
-    // Laplacian 639 -> 153.  Below eight levels the tables, not the columns,
+    // levels, gather -> tiles: O640 FP32 gradient 253 -> 100 us, divergence
+    // 303 -> 107, Laplacian 443 -> 109, divergence and curl 603 -> 146; FP64
+    // divergence 426 -> 186, BF16 Laplacian 373 -> 88; 32 levels FP32
+    // Laplacian 639 -> 143.  Below eight levels the tables, not the columns,
     // are most of the traffic, and a tile's are larger (O640 x 2 FP32
     // divergence 33 -> 40 us, O320 x 4 FP64 Laplacian 30 -> 36); at eight the
     // two are level for the slowest operators (O320 BF16 divergence 17.8 ->
-    // 17.6) and the others gain (FP32 Laplacian 34 -> 27).  In small fields a tile's
+    // 16.1) and the others gain (FP32 Laplacian 34 -> 26).  In small fields a tile's
     // start (tables, then data, then arithmetic: 5-10 us) shows: BF16
     // divergence at 10 levels 7.3 -> 10.2 us at O160, 10.2 -> 11.2 at O200
-    // (1.7 million values), 23.3 -> 19.3 at O320 (4.2 million).  A shape that sets a parameter of
+    // (1.7 million values), 23.3 -> 17.3 at O320 (4.2 million).  A shape that sets a parameter of
     // the gather's keeps it.
     const Shape def;
     if (nlev < kShortTileLevels || V * nlev < kShortTileValues || e.row_window || e.lanes_per_node ||
