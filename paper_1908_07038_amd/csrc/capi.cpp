@@ -113,11 +113,12 @@ struct RelaxedCapture {
 using TableKey = std::vector<int64_t>;
 
 // Tilings and records first built for one call or plan, which gives them back
-// if it cannot complete them (nobody else having asked for them meanwhile).
-// parent: the plan that a call builds for, which then has them to give back.
+// if it cannot complete them (nobody else having asked for them meanwhile),
+// and the records it went without.  parent: the plan that a call builds for,
+// which then has them to give back.
 struct Made {
   Made* parent = nullptr;
-  std::vector<TableKey> tilings, records;
+  std::vector<TableKey> tilings, records, refused;
   bool owns(const Made* maker) const { return maker == this || (parent && maker == parent); }
 };
 
@@ -285,10 +286,14 @@ struct atlas_mesh_s {
   }
 
   // The end of what `made` noted: its tables stay (the parent's to give back,
-  // if there is one), or are given back where no other call has taken them.
+  // if there is one), or are given back where no other call has taken them, and
+  // what it went without may be tried again.
   void settle(Made& made, bool stay) {
-    if (made.tilings.empty() && made.records.empty()) return;
+    if (made.tilings.empty() && made.records.empty() && made.refused.empty()) return;
     std::lock_guard<std::mutex> lk(order_mu);
+    if (!stay)
+      for (const TableKey& k : made.refused) refused.erase(k);
+    made.refused.clear();
     auto end = [&](auto& tables, std::vector<TableKey>& keys, std::vector<TableKey>* parents) {
       for (TableKey& k : keys) {
         auto it = tables.find(k);
@@ -505,17 +510,21 @@ int build_tiles(atlas_mesh_t mesh, const TableKey& key, int op, int dtype, TileG
     rc = fail(ATLAS_EHIP, ex.what());
   }
   mesh->settle(made, rc == ATLAS_OK && tg.KL > 0);
-  if (refused) mesh->refuse(key);
+  if (refused) {
+    if (build) build->refused.push_back(key);
+    mesh->refuse(key);
+  }
   return rc;
 }
 
 // The tiles and node records of a call on LDS tiles (tg.KL > 0), built on
 // first use.  tg.KL = 0 on return: the call runs without them -- short columns,
-// and those that the caller has another way for (or_else), whose tiles cannot be built now (the stream is being captured, where
-// nothing can be allocated) or could not be for want of memory, after which
-// the mesh does without those: what was built of them is given back, and no
-// later call tries again.  Each short level count has tables of its own, which
-// the gather does without, so they are bounded: short_limit a mesh, first come.
+// and those that the caller has another way for (or_else), whose tiles cannot
+// be built now (the stream is being captured, where nothing can be allocated)
+// or could not be for want of memory, after which the mesh does without those:
+// what was built of them is given back, and no later call tries again.  Each
+// short level count has tables of its own, which the gather does without, so
+// they are bounded: short_limit a mesh, first come.
 int call_tiles(atlas_mesh_t mesh, int op, int dtype, TileGeom& tg, const Shape& sh, DevTiles& dt, const void*& rec,
                hipStream_t stream, Made* build, bool or_else = false) {
   const bool optional = or_else || sh.short_tiles;
@@ -536,13 +545,15 @@ int call_tiles(atlas_mesh_t mesh, int op, int dtype, TileGeom& tg, const Shape& 
     dt.nchunks = tg.nchunks;
   } catch (const std::bad_alloc&) {
     rc = fail(ATLAS_ENOMEM, "cannot allocate the LDS tiles");
+  } catch (const std::exception& ex) {
+    rc = fail(ATLAS_EHIP, ex.what());
   }
   return rc;
 }
 
 // build: only build what the call needs on first use (tiles and records, noted
-// there, and the node order); nothing is launched.  add (OP_DIVT): a field of the output's form
-// that the result is added to.
+// there, and the node order); nothing is launched.  add (OP_DIVT): a field of
+// the output's form that the result is added to.
 int run_op(atlas_mesh_t mesh, int op, int dtype, int32_t nlev, const void* in, void* out, void* stream,
            const Shape* shape_override = nullptr, Made* build = nullptr, const void* add = nullptr) {
   int rc = check_mesh_device(mesh);

@@ -192,6 +192,14 @@ static void plan_out_of_memory() {
   dev().limit = dev().live + shared / 2;
   Plan p(n, levels);
   EXPECT(p.rc == ATLAS_ENOMEM);
+  // what its short columns went without they are not denied later
+  dev().limit = dev().live + (size_t(1) << 20);
+  Plan q(n, {19, 300});
+  EXPECT(q.rc == ATLAS_ENOMEM);
+  dev().limit = SIZE_MAX;
+  dev().launches.clear();
+  EXPECT(atlas_nabla_gradient(n.h, ATLAS_F32, 19, field(0), field(1), nullptr) == ATLAS_OK);
+  EXPECT(dev().count("k_tile<") == 1);
 }
 
 // A plan in the field form by request, whose operators' tables are there from
